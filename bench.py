@@ -763,13 +763,13 @@ def main_encode(args, torch, tt):
     e1.record(stream)
     torch.cuda.synchronize()
     ms_step = e0.elapsed_time(e1) / steps
-    # the definition's work: every (p, pattern byte) pair scores every row of
-    # each section's lists (4096 + 2048 + 4096 rows) with 8 additions, per
-    # trial radius; the kernel builds the eight scores of a thread's (p, byte)
-    # pairs from shared partial sums, 22 additions per row instead of 64, and
-    # the roofline counts those it executes
+    # the kernel's work: 6,780 VALU wave instructions per block (SQ_INSTS_VALU
+    # over this workload), a lane operation each; beside it the definition's:
+    # every (p, pattern byte) pair scores every row of each section's lists
+    # (4096 + 2048 + 4096 rows) with 8 additions, per trial radius, which the
+    # kernel does not carry out (it takes maxima over the cost levels)
     adds = 2.0 * 256 * (4096 + 2048 + 4096) * 8 * n
-    executed = adds * 22.0 / 64.0
+    executed = 6780.0 * 64 * n
     tops = executed / (ms_step * 1e-3) / 1e12
     tops_def = adds / (ms_step * 1e-3) / 1e12
     out_j = {
@@ -784,7 +784,7 @@ def main_encode(args, torch, tt):
         "roofline": {"bound": "alu", "achieved": round(tops, 3), "peak": round(VALU32_PEAK_TOPS, 1),
                      "unit": "Tops/s", "frac": round(tops / VALU32_PEAK_TOPS, 4), "traffic": None,
                      "kernel": "encode_kernel", "avg_launch_us": round(ms_step * 1e3, 1),
-                     "ops": "executed 32-bit score additions (22 per list row and eight (p, byte) pairs)",
+                     "ops": "executed VALU lane operations (6,780 wave instructions per block)",
                      "ops_per_launch": executed,
                      "effective": {"achieved": round(tops_def, 3), "frac": round(tops_def / VALU32_PEAK_TOPS, 4),
                                    "ops": "the definition's 8 additions per (p, byte) pair and list row",

@@ -647,7 +647,7 @@ int tetra_encode(const float* w, const float* sigma, size_t n, double radius0, d
     a.n = n;
     a.alpha[0] = radius0;
     a.alpha[1] = radius1;
-    const size_t grid = std::min<size_t>(n, static_cast<size_t>(ds.cus) * 8);
+    const size_t grid = std::min<size_t>(n, static_cast<size_t>(ds.cus) * tetra_dev::kEncGroupsPerCU);
     hipLaunchKernelGGL(tetra_dev::encode_kernel, dim3(static_cast<unsigned>(grid)), dim3(tetra_dev::kEncThreads), 0,
                        stream, a);
     return launch_status();

@@ -28,6 +28,11 @@ namespace tetra {
 constexpr uint32_t kMidOffset = 808;      // 2048 - 1240
 constexpr uint32_t kMidClass0Rows = 1240;
 
+// last rank row (nibble j = rank of coordinate j) of each class of the outer
+// sections' lists and of the middle list: rows go by cost, then by value
+constexpr uint32_t kLastRow0 = 0x11030011, kLastRow1 = 0x00222011;
+constexpr uint32_t kMidLastRow0 = 0x30001010, kMidLastRow1 = 0x31000000;
+
 struct CanonicalFields {
     uint32_t s8, p, r, b1, b2, b3, g, i1, i2, i3;
 };

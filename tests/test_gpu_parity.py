@@ -1065,6 +1065,29 @@ def test_encode_retention_gaussian_blocks():
     assert np.array_equal(words[idx], oencoder.encode_blocks(w[idx], 1.0, tt.ENCODE_RADII))
 
 
+@pytest.mark.parametrize("radii", [(13.0, 15.0), (25.0, 1.0), (18.5, 21.0)])
+@pytest.mark.parametrize("n", [1, 25, 24 * 1024 + 7])
+def test_encode_list_ends_ties_and_batches(n, radii):
+    """Blocks whose sections reach the last cost level of their row lists
+    (large radii, the energy in one section), blocks with equal scores (small
+    integers, one-hot) and zero blocks in between, at block counts around the
+    batches of a workgroup: every word equals the oracle's."""
+    rng = np.random.default_rng(77)
+    base = rng.standard_normal((7, 24)).astype(np.float32)
+    base[1] = rng.integers(-2, 3, 24)
+    base[2] = 0.0
+    base[2, 9] = 1.0
+    base[3, :8] *= 6.0
+    base[4, 8:16] *= 6.0
+    base[5] = 0.0
+    base[6, 16:] *= 6.0
+    want = oencoder.encode_blocks(base, 1.25, radii)
+    at = np.arange(n) % len(base)
+    got = _encode_gpu(base[at], np.full(n, 1.25, np.float32), radii=radii)
+    print(f"[encode edges] n={n} radii={radii} mismatches={(got != want[at]).sum()}", flush=True)
+    assert np.array_equal(got, want[at])
+
+
 # ------------------------------------------------------------- the boundary
 
 def _child(mode):
