@@ -261,14 +261,13 @@ int tetra_decode(const void* words, size_t n, int8_t* y_out, float* blk_scale_ou
  * token's result can change in the last bits with N (it never changes from
  * run to run).
  *   workspace: device memory of the caller, 256-byte aligned, holding
- *              counters and partial sums of the pieces of a launch; it
- *              must be zero-filled before its first use, and every call
- *              leaves it zero-filled again.  Calls that may run at the
- *              same time need different workspaces.
+ *              partial sums of the pieces of a launch (its contents before
+ *              a call do not matter).  Calls that may run at the same time
+ *              need different workspaces.
  *   workspace_bytes: its size; tetra_gemm_workspace_bytes() is the size at
  *              which the product uses every workgroup the device holds (a
- *              smaller workspace runs fewer workgroups, TETRA_EINVAL below
- *              one workgroup's share)
+ *              smaller workspace runs fewer workgroups, or whole items
+ *              only; TETRA_EINVAL below 131,328 bytes)
  * Asynchronous; TETRA_EINVAL / TETRA_EALIGN / TETRA_EDEVICE as for
  * tetra_gemv.
  */
@@ -282,16 +281,15 @@ size_t tetra_gemm_workspace_bytes(void);
 /*
  * tetra_gemm without a workspace argument, for callers that cannot allocate
  * device memory (code under graph capture, serving loops, harnesses that
- * forbid hipMalloc).  The counters and piece sums of the product live in a
- * static scratch array of the library's code object: 67,110,912 bytes per
- * device (the pieces of 512 workgroups, two per CU of a 256-CU MI355X),
+ * forbid hipMalloc).  The piece sums of the product live in a static
+ * scratch array of the library's code object: 67,110,912 bytes per device
+ * (the pieces of 256 workgroups, one per CU of a 256-CU MI355X),
  * held by every device the library runs on until the process ends.  The
  * call runs the same grid as tetra_gemm with a workspace of
  * tetra_gemm_workspace_bytes(), so the two give the same bits; a device
- * that would run more than 512 workgroups is refused (TETRA_EUNSUPPORTED)
+ * that would run more than 256 workgroups is refused (TETRA_EUNSUPPORTED)
  * rather than served with another split.  Input sizes are not limited by
  * the scratch: the pieces scale with the workgroups, not with M, K or N.
- * Each call first clears the scratch's counters with a kernel on `stream`.
  * All calls on one device share its scratch and leave the last call's
  * contents in it: calls that overlap in time on one device (other streams,
  * other threads) race and give wrong results.  Arguments, layouts and the

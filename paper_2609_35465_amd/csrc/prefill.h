@@ -5,60 +5,73 @@
 // y[n][row] = sigma_row * sum_blk s_blk * sum_j y_j x[n][24 blk + j]
 //             + sum_t tail_t x[n][24 nblk + t]
 //
-// is the same sum as the GEMV's.  The decoded
-// y_j are exact integers in fp16; the block's scale is folded into them as
-// fp16(s_blk y_j), rounded once from the fp32 product, so that three
-// v_mfma_f32_32x32x8_f16 (8 k each) per block accumulate straight into the
+// is the same sum as the GEMV's.  The decoded y_j are exact integers in fp16;
+// the block's scale is folded into them as fp16(s_blk y_j), rounded once from
+// the fp32 product, so that the matrix cores accumulate straight into the
 // sums across blocks; sigma and the tail are applied at the end.  The fold
 // costs one rounding of each weight to fp16: a relative error of at most
 // 2^-11 per weight, so at most 2^-11 (4.9e-4) of sum |w x| per output, inside
-// the 1e-3 bound of the products (the GEMV keeps the scale in fp32).  Folding
-// replaced 16 fp32 multiply-adds per block and 32-token group (64 per block
-// at four groups) by the fold's mixed-precision fmas (v_fma_mix: an fp16
-// value times the fp32 scale, rounded once to fp16): 12 per block, against
-// 30 for the conversions, multiplies and packs of a plain fp32 product.  The
-// product is bound by latency, not issue: 82 -> 64 VALU instructions per
-// block and wave left its time unchanged (250-253 TFLOP/s).
+// the 1e-3 bound of the products (the GEMV keeps the scale in fp32).
 //
-// MFMA roles: A = activations (32 tokens x 8 k), B = decoded weights (8 k x
-// 32 rows), D = 32 tokens x 32 rows.  Lane l holds A[l % 32][4h..4h+3] and
-// B[4h..4h+3][l % 32] with h = l / 32, and D[8g + 4h + r][l % 32] in
-// register 4g + r.  So the lanes l and l + 32 of a wave both take row
-// l % 32 of the wave's 32 rows: each decodes the 12 coordinates of a block
-// that its half of the B operand needs (sections 0-2, coordinates 4h..4h+3),
-// the two halves of the norm meet in one lane exchange, and both get the
-// row's block scale, which then scales all 16 outputs of the lane (one row,
-// 16 tokens).
+// MFMA roles (v_mfma_f32_32x32x16_f16): A = activations (32 tokens x 16 k),
+// B = decoded weights (16 k x 32 rows), D = 32 tokens x 32 rows.  Lane l
+// holds A[l % 32][8h..8h+7] and B[8h..8h+7][l % 32] with h = l / 32, and
+// D[8g + 4h + r][l % 32] in register 4g + r.  Blocks go in pairs, a window of
+// 48 k: the lanes of half h decode block h of the pair, one row each, and
+// product kk (of three) takes section kk of both blocks.  So every lane
+// decodes one whole block of its own per window, without any exchange between
+// lanes, and gets all of its row's block scale; the activations are laid out
+// to match.
 //
-// A workgroup of 4 waves takes 128 tokens and either two 64-row tiles (each
-// wave 32 rows by all 128 tokens, four 32-token MFMA groups: every decoded
-// block feeds twelve MFMAs) or one tile (each wave 32 rows by 64 tokens, two
-// groups), chosen per launch (gemm_kernel<TG>).  The activations of the 128
-// tokens go through LDS in chunks of 96 k (one group of four block columns),
-// the decoder tables are staged as in the GEMV.
+// A workgroup of eight waves takes up to 256 tokens (TG groups of 32) and a
+// wave 32 rows by all of them, so that each decoded block feeds TG x 3
+// products.  Two waves share a SIMD (128 accumulators each): one wave alone
+// (64 rows, 512 registers) issues an instruction every five cycles at most
+// and was bound by that, 0.445 ms where this form takes 0.435 (12288 x 4096 by
+// 4096 tokens) and 2.7 us a chunk where it takes 2.3 (20 workgroups).  With S = 1 the waves hold 8 x 32 rows; with S = 2 they hold
+// 4 x 32 rows, and two waves share a row set, one for each window of a chunk,
+// their sums meeting in LDS at the end: half the rows per workgroup, for
+// launches that must be cut into pieces to fill the chip (a piece then is
+// half as large).
 //
-// Work split: an item is a (tile or tile pair, 128-token group) and a unit is
-// one chunk of an item (the trailing block columns of a row make one more,
-// shorter unit).  A fixed number of workgroups (two per CU, fewer for few
-// items) take equal contiguous ranges of the items' units, so no launch
-// leaves most of the chip idle in a last partial wave of workgroups, however
-// many tiles and tokens there are.  An item whose units span several
-// workgroups is combined as in the GEMV: each publishes its sums through the
-// per-device workspace and the last to count in adds the pieces in workgroup
-// order, which makes the result independent of timing.
+// The activations go through LDS in chunks of 96 k (one group of four block
+// columns), double-buffered, one barrier per chunk: the next chunk's are
+// loaded into registers during the first half of a chunk and written to the
+// other buffer during the second.  The decode of the next window is placed
+// between the products of the present one, step by step (pf_step), since the
+// compiler's own order puts the products first and the decode after them.
+//
+// Work split with S = 2 (stream-K): an item is a (row group, token tile) and
+// a unit is one chunk of an item (the trailing block columns of a row make
+// one more, shorter unit).  The workgroups (one per CU, fewer for few items)
+// take equal contiguous ranges of the items' units.  Of an item whose units
+// span several workgroups each stores its sums in the workspace, and a second
+// kernel on the whole chip (gemm_sum_kernel) adds the pieces in workgroup
+// order, which makes the result independent of timing.  (The last workgroup
+// of an item to finish adding them by itself took as long as the product:
+// 1024 x 5120 by 203 tokens 39 us against 22, 5120 x 5120 52 against 37.)
+// With S = 1 every workgroup takes whole items.
+//
+// Measured against a kernel of four waves with 32x32x8 products, each lane
+// decoding half a block, at two workgroups per CU: 12288 x 4096 by 4096
+// tokens 0.86 -> 0.43 ms (950 TFLOP/s, the clock then near 1.6 GHz: the chip
+// is at its power limit), 17408 x 5120 by 203 tokens 125 -> 74 us.
 #pragma once
+
+#include <type_traits>
+#include <utility>
 
 namespace tetra_dev {
 
-constexpr int kPfTokens = 128;             // tokens per workgroup
-constexpr int kPfWaves = 4;
+constexpr int kPfWaves = 8;
 constexpr int kPfThreads = kPfWaves * 64;
-constexpr int kPfChunk = 96;               // k per chunk: four blocks
-constexpr int kPfXStride = 104;            // fp16 per token row of the LDS chunk (96 + 8)
-constexpr int kPfGroupsPerCU = 2;          // 2 x 75 KB of LDS, 2 waves per SIMD
+constexpr int kPfChunk = 96;               // k per chunk: four blocks, two windows
+constexpr int kPfMaxTG = 8;                // 32-token groups of a workgroup, at most
+constexpr int kPfGroupsPerCU = 1;          // 54 KB of tables, up to 96 KB of activations
+constexpr int kPfFrag = 1024;              // bytes of one A operand (32 tokens x 16 k) in LDS
 
-constexpr int kPfMaxTG = 4;                // 32-token MFMA groups per wave, at most
-constexpr int kPfSlot = kPfThreads * 16 * kPfMaxTG;   // floats of one workgroup's piece of an item
+// floats of one workgroup's piece of an item (128 rows by 256 tokens)
+constexpr int kPfSlot = 128 * 32 * kPfMaxTG;
 
 struct GemmArgs {
     const uint8_t* codes;
@@ -67,25 +80,23 @@ struct GemmArgs {
     float* y;                              // [N][M]
     unsigned long long tail_off;
     int M, K, N, nblk, T, ng, rem;
-    int tgroups;                           // token groups of kPfTokens
+    int tgroups;                           // token tiles
     int tiles;                             // 64-row tiles
     int upi;                               // units per item: ng, plus one when rem > 0
+    int items;
     int workers;                           // workgroups of the launch
     unsigned long long units;              // items * upi
-    uint32_t* counters;                    // [workers], zero between launches
     float* partials;                       // [workers][2][kPfSlot]
-    int partial_bytes;                     // size of the partials array
 };
 
-// pieces go through the workspace in 16-byte buffer accesses with the cache
-// policy of device-scope atomics (coherent across the chip's L2 caches):
-// quad q of a thread's sums at byte 16 (256 q + thread) of its slot
 typedef uint32_t pf_u32x4 __attribute__((ext_vector_type(4)));
-constexpr int kPfCoherent = 16;            // sc1
-constexpr int kPfRsrcWord3 = 0x00020000;   // raw 32-bit buffer, gfx9
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t pf_rsrc(const GemmArgs& a) {
-    return __builtin_amdgcn_make_buffer_rsrc(a.partials, static_cast<short>(0), a.partial_bytes, kPfRsrcWord3);
+// a buffer of `bytes` from p (the same for the whole wave): loads from it
+// take a 32-bit lane offset and a scalar one
+constexpr int kPfRsrcWord3 = 0x00020000;   // raw 32-bit buffer, gfx9
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t pf_rsrc(const void* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), static_cast<short>(0), static_cast<int>(bytes),
+                                             kPfRsrcWord3);
 }
 
 // Values pass through these helpers by value: __builtin_bit_cast applied
@@ -99,17 +110,14 @@ __device__ __forceinline__ uint32_t pf_part(const pf_u32x4& v, int i) {
     return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
 }
 
-__device__ __forceinline__ uint32_t pf_slot_bytes(int worker, int side) {
-    return static_cast<uint32_t>((worker * 2 + side) * kPfSlot) * 4u;
-}
-
-// workspace of a launch with at most `workers` workgroups: the counters
-// (rounded up to 256 bytes), then two piece slots per workgroup
-inline size_t gemm_counter_bytes(int workers) {
-    return (sizeof(uint32_t) * static_cast<size_t>(workers) + 255) & ~static_cast<size_t>(255);
+// workspace of a launch with at most `workers` workgroups: a header that
+// nothing uses (eight bytes each, rounded up to 256; the size callers
+// allocate includes it), then two piece slots per workgroup
+inline size_t gemm_header_bytes(int workers) {
+    return (8 * static_cast<size_t>(workers) + 255) & ~static_cast<size_t>(255);
 }
 inline size_t gemm_workspace_bytes(int workers) {
-    return gemm_counter_bytes(workers) + sizeof(float) * static_cast<size_t>(workers) * 2 * kPfSlot;
+    return gemm_header_bytes(workers) + sizeof(float) * static_cast<size_t>(workers) * 2 * kPfSlot;
 }
 
 // a workgroup-uniform 64-bit value in scalar registers (the 64-bit divisions
@@ -132,58 +140,18 @@ __device__ __forceinline__ int pf_worker_of(unsigned long long u, const GemmArgs
         static_cast<int>(((u + 1) * static_cast<unsigned long long>(a.workers) - 1) / a.units));
 }
 
-typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float16_t __attribute__((ext_vector_type(16)));
 
-// the B operand of a block (three 8-k steps, this lane's 4 coordinates of
-// each) and the block's scale
-struct PfBlock {
-    half4_t b[3];
-    float s;
-};
-
-// a block's LDS reads in flight: its table entries and this lane's A
-// operands (two 32-token groups, three 8-k steps)
-struct PfFetch {
-    BlockFetch f;
-    half4_t a[2][3];
-};
-
-// finish a block from its table entries: this lane's half of the values
-// times the block scale (the B operand)
-__device__ __forceinline__ PfBlock pf_decode(const BlockFetch& f, int h, lds_bytes* L) {
-    const uint32_t ep = f.e ^ (~f.pm & 0xFCFCFCFCu);
-    const uint32_t qpair = ~f.pm & 0x3C003C00u;
-    PfBlock o;
-    float sq = 0.f;
-#pragma unroll
-    for (int kk = 0; kk < 3; ++kk) {
-        // coordinates 8 kk + 4h .. 8 kk + 4h + 3: sign group 2 kk + h, row word 2 kk + h
-        const int w = 2 * kk + h;
-        const uint32_t rw = h ? f.r[2 * kk + 1] : f.r[2 * kk];
-        const uint32_t sg = rw ^ ((ep << w) & 0x80808080u);
-        const uint32_t p0 = pk_add(cvt_pair<false>(sg), qpair);
-        const uint32_t p1 = pk_add(cvt_pair<true>(sg), qpair);
-        sq = dot2(p0, p0, sq);
-        sq = dot2(p1, p1, sq);
-        const uint2 u = make_uint2(p0, p1);
-        o.b[kk] = __builtin_bit_cast(half4_t, u);
-    }
-    // the other half's squares (exact integers), then the scale as in the GEMV
-    sq += __shfl_xor(sq, 32, 64);
-    const float sqb = __builtin_bit_cast(float, f.bias) + sq;
-    o.s = *(lds_f32*)(L + kScaleOff + ((__builtin_bit_cast(uint32_t, sqb) >> 2) & 0x7FFu));
-#pragma unroll
-    for (int kk = 0; kk < 3; ++kk)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o.b[kk][i] = static_cast<_Float16>(__builtin_fmaf(static_cast<float>(o.b[kk][i]), o.s, 0.0f));
-    return o;
+// f(constant 0) .. f(constant N - 1): the product loop is unrolled by the
+// front end (the optimizer gives up on loops of this size)
+template <int... I, class F>
+__device__ __forceinline__ void pf_for_impl(std::integer_sequence<int, I...>, F&& f) {
+    (f(std::integral_constant<int, I>{}), ...);
 }
-
-// this lane's A operand for a block and 8-k step: token row tok of the LDS
-// chunk, k = 24 blk + 8 kk + 4h
-__device__ __forceinline__ half4_t pf_a(const _Float16* s_x, int tok, int blk, int kk, int h) {
-    return *reinterpret_cast<const half4_t*>(s_x + tok * kPfXStride + 24 * blk + 8 * kk + 4 * h);
+template <int N, class F>
+__device__ __forceinline__ void pf_for(F&& f) {
+    pf_for_impl(std::make_integer_sequence<int, N>{}, f);
 }
 
 // this thread's index in the workgroup, read afresh at each use: an index
@@ -193,314 +161,417 @@ __device__ __forceinline__ int pf_tid() {
     return (__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x)) & ~63) | lane_now();
 }
 
-// a full chunk of the workgroup's activations (128 tokens x 96 k) in
-// registers: six 16-byte pieces per thread, loaded while the previous chunk
-// is being used and written to LDS after it
-constexpr int kPfPieces = kPfTokens * (kPfChunk / 8) / kPfThreads;
-static_assert(kPfPieces * kPfThreads == kPfTokens * (kPfChunk / 8), "whole pieces per thread");
-
-// one 24-dword vector rather than an array of six uint4: the array form was
-// placed in scratch memory across the item loop
-typedef uint32_t pf_u24 __attribute__((ext_vector_type(4 * kPfPieces)));
-struct PfXRegs {
-    pf_u24 v;
+// the B operands of a window (three 16-k steps): this lane's block
+struct PfBlock {
+    pf_u32x4 b[3];
 };
 
-// where this thread's pieces of every chunk of an item come from and go to:
-// piece i is 16 bytes of token tok_i at k offset 8 q_i of the chunk.  Byte
-// offsets from x for chunk 0 (32-bit: the entry point keeps N K 2 below
-// 2^31) and into the LDS chunk.  Tokens past N read row N-1: their products
-// only reach outputs that are never stored.
-struct PfXMap {
-    uint32_t g[kPfPieces];
-    uint32_t l[kPfPieces];
+// the decode of a block in flight
+struct PfDecode {
+    uint32_t e, r[6], pm, a1, am, u3, ep, qp, sg, y[12];
+    float sa, sb, s, t[4];
 };
 
-__device__ __forceinline__ PfXMap pf_map(const GemmArgs& a, int n0) {
-    PfXMap m;
-    const int t = pf_tid();
+// The decode of one block per lane (word lo, hi) as kPfSteps steps of a few
+// instructions each: the table reads, the values with their norm (as
+// fetch_block and block_values form them), the scale's read, and the values
+// times the scale, rounded once from the fp32 product.  v_fma_mix_f32 twice
+// and one v_cvt_pk_f16_f32 per pair: the mixed fmas that write half a
+// register (v_fma_mixlo / mixhi) take 8.6 cycles each against 5.3, so the
+// pair is kept from being formed that way.
+constexpr int kPfSteps = 5 + 24 + 1 + 18;
+
+template <int n>
+__device__ __forceinline__ void pf_step(PfDecode& d, PfBlock& o, uint32_t lo, uint32_t hi, lds_bytes* L) {
+    if constexpr (n == 0) {
+        d.e = *(lds_u32*)(L + kPathOff + ((lo << 2) & 0x3FFCu));                 // 4 * path
+        uint32_t i2 = __builtin_amdgcn_alignbit(hi, lo, 25) & 0x7FFu;
+        asm("" : "+v"(i2));
+        d.am = i2 * 8u + 8u * tetra::kMidOffset;                                 // 8 * (808 + i2), bit 14 = delta
+        asm("" : "+v"(d.am));
+    } else if constexpr (n == 1) {
+        d.a1 = (lo >> 10) & 0x7FF8u;                                             // 8 * phys1
+        const u32x2 r1 = *(lds_u2*)(L + kRowsOff + d.am);
+        const u32x2 r0 = *(lds_u2*)(L + kRowsOff + d.a1);
+        d.r[0] = r0.x;
+        d.r[1] = r0.y;
+        d.r[2] = r1.x;
+        d.r[3] = r1.y;
+    } else if constexpr (n == 2) {
+        d.u3 = (hi >> 1) & 0x7FF8u;                                              // 8 * ((p ^ r) << 11 | i3')
+        const uint32_t a3 = d.u3 ^ (d.am & 0x4000u);                             // 8 * phys3 (Eq. 3)
+        const u32x2 r2 = *(lds_u2*)(L + kRowsOff + a3);
+        d.r[4] = r2.x;
+        d.r[5] = r2.y;
+    } else if constexpr (n == 3) {
+        d.pm = static_cast<uint32_t>(static_cast<int32_t>((d.a1 ^ d.u3) << 17) >> 31);   // p = r ^ (p ^ r)
+        d.sa = pf_float((lo & 0x1000u) | 0x4B000000u);                           // 2^23 + 4096 g
+        d.sb = 0.f;
+    } else if constexpr (n == 4) {
+        d.ep = d.e ^ (~d.pm & 0xFCFCFCFCu);
+        d.qp = ~d.pm & 0x3C003C00u;
+    } else if constexpr (n < 29) {
+        constexpr int k = (n - 5) >> 2, q = (n - 5) & 3;
+        if constexpr (q == 0) {
+            d.sg = d.r[k] ^ ((d.ep << k) & 0x80808080u);
+        } else if constexpr (q == 1) {
+            d.y[2 * k] = cvt_pair<false>(d.sg);
+            d.y[2 * k + 1] = cvt_pair<true>(d.sg);
+        } else if constexpr (q == 2) {
+            d.y[2 * k] = pk_add(d.y[2 * k], d.qp);
+            d.y[2 * k + 1] = pk_add(d.y[2 * k + 1], d.qp);
+        } else {
+            d.sa = dot2(d.y[2 * k], d.y[2 * k], d.sa);
+            d.sb = dot2(d.y[2 * k + 1], d.y[2 * k + 1], d.sb);
+        }
+    } else if constexpr (n == 29) {
+        d.s = *(lds_f32*)(L + kScaleOff + ((pf_bits(d.sa + d.sb) >> 2) & 0x7FFu));
+    } else {
+        constexpr int k = (n - 30) / 3, q = (n - 30) % 3;
+        if constexpr (q < 2) {
+            const half2_t h = __builtin_bit_cast(half2_t, d.y[2 * k + q]);
+            float u = __builtin_fmaf(static_cast<float>(h[0]), d.s, 0.f);
+            float v = __builtin_fmaf(static_cast<float>(h[1]), d.s, 0.f);
+            asm("" : "+v"(u));
+            asm("" : "+v"(v));
+            d.t[2 * q] = u;
+            d.t[2 * q + 1] = v;
+        } else {
 #pragma unroll
-    for (int i = 0; i < kPfPieces; ++i) {
-        const int idx = t + i * kPfThreads;
-        const int tok = idx / (kPfChunk / 8), q = idx - tok * (kPfChunk / 8);
-        m.g[i] = static_cast<uint32_t>(min(n0 + tok, a.N - 1)) * static_cast<uint32_t>(2 * a.K) + 16u * q;
-        m.l[i] = static_cast<uint32_t>(tok * (2 * kPfXStride) + 16 * q);
-    }
-    return m;
-}
-
-__device__ __forceinline__ void pf_load_x(PfXRegs& r, const GemmArgs& a, const PfXMap& m, int k0) {
-    const uint8_t* base = reinterpret_cast<const uint8_t*>(a.x + k0);
-#pragma unroll
-    for (int i = 0; i < kPfPieces; ++i) {
-        const uint4 t = *reinterpret_cast<const uint4*>(base + m.g[i]);
-        r.v[4 * i] = t.x;
-        r.v[4 * i + 1] = t.y;
-        r.v[4 * i + 2] = t.z;
-        r.v[4 * i + 3] = t.w;
+            for (int i = 0; i < 2; ++i) {
+                half2_t v;
+                v[0] = static_cast<_Float16>(d.t[2 * i]);
+                v[1] = static_cast<_Float16>(d.t[2 * i + 1]);
+                o.b[(2 * k + i) >> 2][(2 * k + i) & 3] = __builtin_bit_cast(uint32_t, v);
+            }
+        }
     }
 }
 
-__device__ __forceinline__ void pf_store_x(_Float16* s_x, const PfXRegs& r, const PfXMap& m) {
-#pragma unroll
-    for (int i = 0; i < kPfPieces; ++i)
-        *reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(s_x) + m.l[i]) =
-            make_uint4(r.v[4 * i], r.v[4 * i + 1], r.v[4 * i + 2], r.v[4 * i + 3]);
-}
+// a lane's code words of a chunk: its row's block 2j + h for the windows j
+struct PfWords {
+    uint32_t lo[2], hi[2];
+};
 
-// activations of the workgroup's tokens for k0 .. k0 + cols - 1 into LDS
-// (zero for tokens past N); cols is a multiple of 8 and at most 96
-__device__ __forceinline__ void pf_stage_x(_Float16* s_x, const GemmArgs& a, int n0, int k0, int cols) {
-    const int per_tok = cols / 8;                        // 16-byte pieces per token
-    for (int i = pf_tid(); i < kPfTokens * per_tok; i += kPfThreads) {
-        const int tok = i / per_tok, q = i - tok * per_tok;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (n0 + tok < a.N)
-            v = *reinterpret_cast<const uint4*>(a.x + static_cast<size_t>(n0 + tok) * a.K + k0 + 8 * q);
-        *reinterpret_cast<uint4*>(s_x + tok * kPfXStride + 8 * q) = v;
-    }
-}
-
-// TG = 4: an item is two tiles (128 rows) by 128 tokens and each wave takes
-// 32 rows by all 128 tokens, so that every decoded block feeds four token
-// groups.  TG = 2: an item is one tile by 128 tokens, each wave 32 rows by
-// 64 tokens; items are then half the size, for shapes with few rows, whose
-// items would otherwise be cut into many pieces.
+// a chunk of the activations in flight: a token's 192 bytes are twelve
+// 16-byte pieces; a thread holds pieces xq, xq + 4 and xq + 8 of one token in
+// every 128, so that four threads read 64 bytes of a token at once
 template <int TG>
-__global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2))) void gemm_kernel(const GemmArgs a) {
+struct PfX {
+    static constexpr int kIt = (TG + 3) / 4;
+    typedef uint32_t vec_t __attribute__((ext_vector_type(12 * kIt)));
+    vec_t v;
+};
+
+// LDS bytes of a chunk buffer: fragments [token group][window][kk], token
+// groups in fours; two of them also take the sums that waves exchange
+template <int TG>
+constexpr int pf_buf_bytes() {
+    return (TG + 3) / 4 * 4 * 6 * kPfFrag;
+}
+
+template <int TG, int S>
+__global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_kernel(const GemmArgs a) {
+    static_assert(S == 1 || S == 2, "windows of a chunk per wave: two or one");
     __shared__ uint4 s_tab[kPackedTableBytes / 16];
-    __shared__ __attribute__((aligned(16))) _Float16 s_x[kPfTokens * kPfXStride];
-    __shared__ uint32_t s_arrived;
-    stage_packed_tables<kPfThreads>(s_tab);
+    __shared__ __attribute__((aligned(16))) uint8_t s_x[2][pf_buf_bytes<TG>()];
+    TableStage<kPfThreads> ts;
+    ts.load();                                             // stored below, after the ranges are worked out
     lds_bytes* L = (lds_bytes*)(s_tab);
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int h = lane >> 5, jr = lane & 31;
-    const int rin = (wave & 1) * 32 + jr;                 // row in the wave's 64-row tile
-    const int tok0 = TG == 4 ? 0 : (wave >> 1) * 64;      // first of the wave's tokens in the chunk
-    const int w = blockIdx.x;
+    constexpr int kRowSets = kPfWaves / S;                 // 32-row sets of a workgroup
+    constexpr int kSlots = 3 * TG;                         // products of a window
+    constexpr int kAhead = 3;                              // A operands read ahead
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    const int rset = S == 1 ? wave : wave >> 1, ksplit = S == 1 ? 0 : wave & 1;
+    const int lane = threadIdx.x & 63, h = lane >> 5, jr = lane & 31;
+    // LDS byte of this lane's A operand of product kk in window j (S = 2: in
+    // this wave's window), piece q = 6 j + 3 h + kk of its token: the tokens
+    // of a half fragment are permuted by 4 (q mod 4), so that neither the
+    // reads (16 lanes of a half at once) nor the writes (four pieces of four
+    // tokens) meet in a bank
+    uint32_t ar[2][3];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int kk = 0; kk < 3; ++kk) {
+            const int jj = S == 2 ? ksplit : j;
+            ar[j][kk] = static_cast<uint32_t>((3 * jj + kk) * kPfFrag + 512 * h +
+                                              16 * (jr ^ (4 * ((6 * jj + 3 * h + kk) & 3))));
+        }
+    // this thread's pieces of a chunk: xq + 4 i of token xtok + 128 it
+    const int xtok = threadIdx.x >> 2, xq = threadIdx.x & 3;
+    uint32_t xl[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int q = xq + 4 * i, b = q / 3, kk = q - 3 * b;
+        xl[i] = static_cast<uint32_t>(((xtok >> 5) * 6 + 3 * (b >> 1) + kk) * kPfFrag + 512 * (b & 1) +
+                                      16 * ((xtok & 31) ^ (4 * xq)));
+    }
+    const uint32_t wlo = static_cast<uint32_t>(16 * (32 * (rset & 1) + jr) + 4 * h + 8 * ksplit);
+    const uint32_t whi = static_cast<uint32_t>(1024 + 8 * (32 * (rset & 1) + jr) + 2 * h + 4 * ksplit);
+    const __amdgpu_buffer_rsrc_t xrs = pf_rsrc(a.x, static_cast<uint32_t>(2 * a.K) * static_cast<uint32_t>(a.N));
     float16_t acc[TG];
 
-    // the A operands of 32-token groups tg0, tg0 + 1 for a block
-    auto load_a = [&](int blk, int tg0, half4_t (&av)[2][3]) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int kk = 0; kk < 3; ++kk) av[q][kk] = pf_a(s_x, tok0 + 32 * (tg0 + q) + jr, blk, kk, h);
-    };
-    auto issue = [&](uint32_t lo, uint32_t hi, int blk, PfFetch& pf) {
-        pf.f = fetch_block(lo, hi, L);
-        load_a(blk, 0, pf.a);
-    };
-    // blocks 0 .. nb-1 of the staged chunk (words lo[k], hi[k]) as a pipeline:
-    // while a block's products run on the matrix cores, the next block's LDS
-    // reads are in flight and its values are formed on the vector unit.  The
-    // four token groups go in two pairs; the second pair's activations are
-    // read while the first pair's products run.
-    auto run_chunk = [&](const uint32_t (&lo)[4], const uint32_t (&hi)[4], int nb) {
-        PfFetch nx;
-        issue(lo[0], hi[0], 0, nx);
-        PfBlock cur = pf_decode(nx.f, h, L);
-        half4_t a01[2][3];
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int kk = 0; kk < 3; ++kk) a01[q][kk] = nx.a[q][kk];
-        for (int blk = 0; blk < nb; ++blk) {
-            const bool more = blk + 1 < nb;
-            if (more) issue(lo[min(blk + 1, 3)], hi[min(blk + 1, 3)], blk + 1, nx);
-#pragma unroll
-            for (int kk = 0; kk < 3; ++kk)
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-                    acc[q] = __builtin_amdgcn_mfma_f32_32x32x8f16(a01[q][kk], cur.b[kk], acc[q], 0, 0, 0);
-            half4_t a23[2][3];
-            if constexpr (TG == 4) load_a(blk, 2, a23);
-            PfBlock nxt;
-            if (more) nxt = pf_decode(nx.f, h, L);
-            if constexpr (TG == 4) {
-#pragma unroll
-                for (int kk = 0; kk < 3; ++kk)
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-                        acc[2 + q] = __builtin_amdgcn_mfma_f32_32x32x8f16(a23[q][kk], cur.b[kk], acc[2 + q], 0, 0, 0);
-            }
-            if (more) {
-                cur = nxt;
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-#pragma unroll
-                    for (int kk = 0; kk < 3; ++kk) a01[q][kk] = nx.a[q][kk];
-            }
-        }
-    };
-    // sigma and the unquantised tail applied to an item's sums v for the
-    // wave's tile wt (only when it holds rows); this lane's row, 16 tokens per
-    // group
-    auto finish = [&](const float16_t (&v)[TG], int wt, bool live, int n0) {
-        // lane indices read afresh: derived from threadIdx they would be
-        // computed once for all items and held in registers throughout
-        const int ln = lane_now();
-        const int fh = ln >> 5;
-        const int frin = (__builtin_amdgcn_readfirstlane(threadIdx.x) & 64) / 2 + (ln & 31);
-        const int ftok0 = TG == 4 ? 0 : (__builtin_amdgcn_readfirstlane(threadIdx.x) & 128) / 2;
-        __syncthreads();
-        // the tail columns of the tokens' activations, 4 bytes at a time (T is even)
-        for (int i = pf_tid(); i < kPfTokens * (a.T >> 1); i += kPfThreads) {
-            const int tok = i / (a.T >> 1), q = i - tok * (a.T >> 1);
-            uint32_t xv = 0;
-            if (n0 + tok < a.N)
-                xv = *reinterpret_cast<const uint32_t*>(a.x + static_cast<size_t>(n0 + tok) * a.K + 24 * a.nblk +
-                                                        2 * q);
-            *reinterpret_cast<uint32_t*>(s_x + tok * kPfXStride + 2 * q) = xv;
-        }
-        __syncthreads();
-        const int row = wt * kTile + frin;
-        if (live && row < a.M) {
-            const float sg = f16(a.sigma[row]);
-            const uint32_t* tl =
-                reinterpret_cast<const uint32_t*>(a.codes + a.tail_off) + static_cast<size_t>(row) * (a.T >> 1);
-            uint32_t tv[11];
-#pragma unroll
-            for (int q = 0; q < 11; ++q) tv[q] = 2 * q < a.T ? tl[q] : 0u;
-#pragma unroll
-            for (int tg = 0; tg < TG; ++tg)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int tok = ftok0 + 32 * tg + 8 * (e >> 2) + 4 * fh + (e & 3);
-                    if (n0 + tok >= a.N) continue;
-                    const uint32_t* xt = reinterpret_cast<const uint32_t*>(s_x + tok * kPfXStride);
-                    float ts = 0.f;
-#pragma unroll
-                    for (int q = 0; q < 11; ++q)
-                        if (2 * q < a.T) ts = dot2(tv[q], xt[q], ts);
-                    a.y[static_cast<size_t>(n0 + tok) * a.M + row] = fmaf(sg, v[tg][e], ts);
-                }
-        }
-    };
-
-    const unsigned long long u0 = pf_range_begin(w, a), u1 = pf_range_begin(w + 1, a);
-    for (unsigned long long base = pf_uniform(u0 - u0 % a.upi); base < u1; base += a.upi) {
-        // this workgroup's units c0 .. c1-1 of the item starting at unit base
-        const int item = __builtin_amdgcn_readfirstlane(static_cast<int>(base / a.upi));
-        const int c0 = __builtin_amdgcn_readfirstlane(static_cast<int>((u0 > base ? u0 : base) - base));
-        const int c1 = __builtin_amdgcn_readfirstlane(static_cast<int>((u1 < base + a.upi ? u1 : base + a.upi) - base));
+    const unsigned long long u0 = S == 1 ? 0 : pf_range_begin(blockIdx.x, a);
+    const unsigned long long u1 = S == 1 ? 0 : pf_range_begin(blockIdx.x + 1, a);
+    unsigned long long base = S == 1 ? 0 : pf_uniform(u0 - u0 % a.upi);
+    ts.store(s_tab);
+    for (int item = S == 1 ? static_cast<int>(blockIdx.x) : __builtin_amdgcn_readfirstlane(static_cast<int>(base / a.upi));
+         S == 1 ? item < a.items : base < u1; item += S == 1 ? a.workers : 1, base += a.upi) {
+        // this workgroup's units c0 .. c1-1 of the item
+        const int c0 = S == 1 ? 0 : __builtin_amdgcn_readfirstlane(static_cast<int>((u0 > base ? u0 : base) - base));
+        const int c1 = S == 1 ? a.upi
+                              : __builtin_amdgcn_readfirstlane(static_cast<int>((u1 < base + a.upi ? u1 : base + a.upi) - base));
         const int irow = item / a.tgroups;
-        const int n0 = (item - irow * a.tgroups) * kPfTokens;
-        // the wave's tile: with TG = 4 waves 0-1 take the item's first tile and
-        // waves 2-3 the second (past the last tile they repeat it and store
-        // nothing); with TG = 2 all four take the item's tile
-        const int wt_raw =
-            TG == 4 ? 2 * irow + (__builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x)) >> 7) : irow;
-        const bool live = wt_raw < a.tiles;
+        const int n0 = (item - irow * a.tgroups) * (32 * TG);
+        // the wave's row set; past the last tile it repeats that and stores nothing
+        const int wt_raw = (irow * kRowSets + rset) >> 1;
         const int wt = min(wt_raw, a.tiles - 1);
         const uint8_t* tb = a.codes + static_cast<size_t>(wt) * a.nblk * kChunk;
+        const __amdgpu_buffer_rsrc_t tr = pf_rsrc(tb, static_cast<uint32_t>(a.nblk) * kChunk);
+        uint32_t xg[PfX<TG>::kIt];                         // tokens past N read row N - 1: never stored
 #pragma unroll
-        for (int tg = 0; tg < TG; ++tg)
+        for (int it = 0; it < PfX<TG>::kIt; ++it)
+            xg[it] = static_cast<uint32_t>(min(n0 + 128 * it + xtok, a.N - 1)) * static_cast<uint32_t>(2 * a.K) + 16u * xq;
+        constexpr int kPieces = 3 * PfX<TG>::kIt;
+        PfX<TG> xr;
+        PfWords wc, wn;
+        // chunk c; the trailing columns (c = ng) are zero past the last block,
+        // and their words past it decode to the origin
+        auto load_x = [&](int c) {
+            auto get = [&](auto p, uint32_t at) {
+                const pf_u32x4 q = __builtin_amdgcn_raw_buffer_load_b128(xrs, at, 2 * kPfChunk * c, 0);
+                xr.v[4 * p] = q.x;
+                xr.v[4 * p + 1] = q.y;
+                xr.v[4 * p + 2] = q.z;
+                xr.v[4 * p + 3] = q.w;
+            };
+            if (c < a.ng)
+                pf_for<kPieces>([&](auto p) { get(p, xg[p / 3] + 64 * (p % 3)); });
+            else                                           // past the last block: out of the buffer, which reads zero
+                pf_for<kPieces>([&](auto p) {
+                    get(p, xq + 4 * (p % 3) < 3 * a.rem ? xg[p / 3] + 64 * (p % 3) : 0x80000000u);
+                });
+        };
+        auto store_x = [&](uint8_t* dst, auto p) {         // piece p % 3 of token xtok + 128 (p / 3)
+            *reinterpret_cast<uint4*>(dst + xl[p % 3] + 24 * (p / 3) * kPfFrag) =
+                make_uint4(xr.v[4 * p], xr.v[4 * p + 1], xr.v[4 * p + 2], xr.v[4 * p + 3]);
+        };
+        auto load_w = [&](PfWords& w, int c) {
+            if (c < a.ng) {
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[tg][e] = 0.f;
+                for (int j = 0; j < 2; ++j) {
+                    if (S == 2 && j == 1) continue;
+                    w.lo[j] = __builtin_amdgcn_raw_buffer_load_b32(tr, wlo + 8 * j, c * tetra::kGroupBytes, 0);
+                    w.hi[j] = static_cast<uint16_t>(
+                        __builtin_amdgcn_raw_buffer_load_b16(tr, whi + 4 * j, c * tetra::kGroupBytes, 0));
+                }
+            } else {
+                const int ln = lane_now();
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    if (S == 2 && j == 1) continue;
+                    const int q = 2 * (S == 2 ? ksplit : j) + (ln >> 5);
+                    const tetra::WordLoc at = tetra::word_loc(a.nblk, 32 * (rset & 1) + (ln & 31), 4 * a.ng + min(q, a.rem - 1));
+                    w.lo[j] = *reinterpret_cast<const uint32_t*>(tb + at.lo_off);
+                    w.hi[j] = *reinterpret_cast<const uint16_t*>(tb + at.hi_off);
+                    if (q >= a.rem) {
+                        w.lo[j] = tetra::kZeroLo;
+                        w.hi[j] = tetra::kZeroHi;
+                    }
+                }
+            }
+        };
+        PfDecode d;
+        PfBlock ba, bb;
+        half8_t av[kAhead + 1];
+        auto frag = [&](const uint8_t* xs, const uint32_t (&at)[3], int slot) {
+            return *reinterpret_cast<const half8_t*>(xs + at[slot / TG] + 6 * (slot % TG) * kPfFrag);
+        };
+        // the products of the window at `at` of the chunk xs with `cur`, and
+        // between them the decode of the words lo, hi into `nxt`
+        auto window = [&](const uint8_t* xs, const uint32_t (&at)[3], const PfBlock& cur, PfBlock& nxt, uint32_t lo, uint32_t hi,
+                          auto&& also) {
+            pf_for<kAhead>([&](auto s) {
+                if constexpr (s < kSlots) av[s] = frag(xs, at, s);
+            });
+            pf_for<kSlots>([&](auto s) {
+                if constexpr (s + kAhead < kSlots) av[(s + kAhead) % (kAhead + 1)] = frag(xs, at, s + kAhead);
+                acc[s % TG] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                    av[s % (kAhead + 1)], __builtin_bit_cast(half8_t, cur.b[s / TG]), acc[s % TG], 0, 0, 0);
+                also(s);
+                constexpr int i0 = s * kPfSteps / kSlots, i1 = (s + 1) * kPfSteps / kSlots;
+                pf_for<i1 - i0>([&](auto i) { pf_step<i0 + i>(d, nxt, lo, hi, L); });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        };
+        // the stores of the next chunk spread over a window's second part
+        auto put_next = [&](uint8_t* dst, auto s) {
+            constexpr int first = kSlots / 2;
+            constexpr int p0 = s < first ? 0 : (s - first) * kPieces / (kSlots - first);
+            constexpr int p1 = s < first ? 0 : (s + 1 - first) * kPieces / (kSlots - first);
+            pf_for<p1 - p0>([&](auto p) { store_x(dst, std::integral_constant<int, p0 + p>{}); });
+        };
 
-        // whole chunks: the next chunk's activations and code words are loaded
-        // into registers while the current one runs
-        const int g1 = min(c1, a.ng);
-        if (c0 < g1) {
-            const PfXMap xm = pf_map(a, n0);
-            PfXRegs xr;
-            pf_load_x(xr, a, xm, kPfChunk * c0);
-            const uint8_t* gp0 = tb + static_cast<size_t>(c0) * tetra::kGroupBytes;
-            uint4 l4 = *reinterpret_cast<const uint4*>(gp0 + 16 * rin);
-            uint2 h2 = *reinterpret_cast<const uint2*>(gp0 + 1024 + 8 * rin);
-            for (int g = c0; g < g1; ++g) {
-                __syncthreads();                          // the previous chunk has been read
-                pf_store_x(s_x, xr, xm);
-                __syncthreads();
-                const uint32_t lo[4] = {l4.x, l4.y, l4.z, l4.w};
-                const uint32_t hi[4] = {h2.x, h2.x >> 16, h2.y, h2.y >> 16};
-                if (g + 1 < g1) {
-                    const uint8_t* gp = tb + static_cast<size_t>(g + 1) * tetra::kGroupBytes;
-                    pf_load_x(xr, a, xm, kPfChunk * (g + 1));
-                    l4 = *reinterpret_cast<const uint4*>(gp + 16 * rin);
-                    h2 = *reinterpret_cast<const uint2*>(gp + 1024 + 8 * rin);
-                }
-                run_chunk(lo, hi, 4);
-            }
-        }
-        if (a.rem > 0 && c1 == a.upi) {
-            // the trailing columns: the words of row rin (word_loc gives them for
-            // any lane's row)
-            uint32_t lo[4], hi[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const tetra::WordLoc at = tetra::word_loc(a.nblk, rin, 4 * a.ng + min(k, a.rem - 1));
-                lo[k] = *reinterpret_cast<const uint32_t*>(tb + at.lo_off);
-                hi[k] = *reinterpret_cast<const uint16_t*>(tb + at.hi_off);
+        for (int t = 0; t < TG; ++t)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[t][e] = 0.f;
+        load_w(wc, c0);
+        load_x(c0);
+        __syncthreads();                                   // tables staged; LDS of the previous item read
+        pf_for<kPieces>([&](auto p) { store_x(s_x[c0 & 1], p); });
+        pf_for<kPfSteps>([&](auto i) { pf_step<i>(d, ba, wc.lo[0], wc.hi[0], L); });
+        __syncthreads();
+        for (int c = c0; c < c1; ++c) {
+            const uint8_t* xs = s_x[c & 1];
+            uint8_t* dst = s_x[(c & 1) ^ 1];
+            const int cn = min(c + 1, c1 - 1);             // past the last: it again, not used
+            load_w(wn, cn);
+            load_x(cn);
+            if constexpr (S == 1) {
+                window(xs, ar[0], ba, bb, wc.lo[1], wc.hi[1], [&](auto) {});
+                window(xs, ar[1], bb, ba, wn.lo[0], wn.hi[0], [&](auto s) { put_next(dst, s); });
+            } else {
+                window(xs, ar[0], ba, bb, wn.lo[0], wn.hi[0], [&](auto s) { put_next(dst, s); });
+                ba = bb;
             }
+            wc = wn;
             __syncthreads();
-            pf_stage_x(s_x, a, n0, kPfChunk * a.ng, 24 * a.rem);
-            __syncthreads();
-            run_chunk(lo, hi, a.rem);
-        }
-        if (c0 == 0 && c1 == a.upi) {
-            finish(acc, wt, live, n0);
-            continue;
         }
 
-        // a piece of an item that other workgroups share.  Slot 0 of a workgroup
-        // holds the piece of the item where its range starts, slot 1 that of
-        // the item where it ends.  The sums and the counters are accessed only
-        // with device-scope atomics, coherent across the chip's L2 caches; the
-        // wait orders each thread's sums before the barrier and the count.
-        const __amdgpu_buffer_rsrc_t rs = pf_rsrc(a);
-        {
-            const uint32_t mine = pf_slot_bytes(w, u0 >= base ? 0 : 1) + 16u * static_cast<uint32_t>(pf_tid());
+        // S = 2: the two waves of a row set add their sums, the first TH token
+        // groups in the one and the others in the other
+        constexpr int TH = S == 1 ? TG : (TG + 1) / 2;
+        const int t0 = S == 1 ? 0 : ksplit * TH;           // first of this wave's token groups, then in acc[0 .. TH-1]
+        if constexpr (S == 2) {
+            pf_u32x4* ex = reinterpret_cast<pf_u32x4*>(s_x[0]) + rset * (TH * 256) + lane_now();
+            static_assert(kPfWaves / 2 * TH * 4096 <= 2 * pf_buf_bytes<TG>(), "exchange fits the chunk buffers");
+            auto give = [&](auto first) {
+                pf_for<TH>([&](auto t) {
+                    if constexpr (first + t < TG)
 #pragma unroll
-            for (int tg = 0; tg < TG; ++tg)
+                        for (int k = 0; k < 4; ++k)
+                            ex[(4 * t + k) * 64] =
+                                pf_u32x4{pf_bits(acc[first + t][4 * k]), pf_bits(acc[first + t][4 * k + 1]),
+                                         pf_bits(acc[first + t][4 * k + 2]), pf_bits(acc[first + t][4 * k + 3])};
+                });
+            };
+            auto take = [&](auto first) {
+                pf_for<TH>([&](auto t) {
+                    if constexpr (first + t < TG)
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const pf_u32x4 q = {pf_bits(acc[tg][4 * k]), pf_bits(acc[tg][4 * k + 1]),
-                                        pf_bits(acc[tg][4 * k + 2]), pf_bits(acc[tg][4 * k + 3])};
-                    __builtin_amdgcn_raw_buffer_store_b128(q, rs, mine + 16u * kPfThreads * (4 * tg + k), 0,
-                                                           kPfCoherent);
-                }
+                        for (int k = 0; k < 4; ++k) {
+                            const pf_u32x4 o = ex[(4 * t + k) * 64];
+#pragma unroll
+                            for (int i = 0; i < 4; ++i)
+                                acc[t][4 * k + i] = acc[first + t][4 * k + i] + pf_float(pf_part(o, i));
+                        }
+                });
+            };
+            constexpr std::integral_constant<int, 0> lower;
+            constexpr std::integral_constant<int, TH> upper;
+            if (ksplit == 1) give(lower);
+            __syncthreads();
+            if (ksplit == 0) take(lower);
+            __syncthreads();
+            if (ksplit == 0) give(upper);
+            __syncthreads();
+            if (ksplit == 1) take(upper);
+            __syncthreads();
         }
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-        const int wf = pf_worker_of(base, a), wl = pf_worker_of(base + a.upi - 1, a);
-        __syncthreads();
-        if (threadIdx.x == 0)
-            s_arrived = __hip_atomic_fetch_add(a.counters + wf, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        if (s_arrived != static_cast<uint32_t>(wl - wf)) continue;
-        // the last piece in: add all of them in workgroup order (its own piece
-        // too, read back like the others), PB pieces per round trip
-        constexpr int PB = TG == 4 ? 2 : 4;
-        const int side_wf = pf_range_begin(wf, a) >= base ? 0 : 1;
+
+        // sigma, and in the item's last piece the unquantised tail (one product:
+        // T is 0, 8 or 16); this lane's row, 16 tokens per group
+        const int ln = lane_now();
+        const int fh = ln >> 5, fj = ln & 31;
+        const int row = wt * kTile + 32 * (rset & 1) + fj;
+        const bool live = wt_raw < a.tiles && row < a.M;
+        const float sg = f16(a.sigma[min(row, a.M - 1)]);
+        pf_u32x4 bt = {0, 0, 0, 0};
+        if (8 * fh < a.T)
+            bt = *reinterpret_cast<const pf_u32x4*>(a.codes + a.tail_off +
+                                                    2 * (static_cast<size_t>(min(row, a.M - 1)) * a.T + 8 * fh));
+        const bool whole = c0 == 0 && c1 == a.upi, tail = a.T > 0 && c1 == a.upi;
+        auto load_tail = [&](int t) {
+            const uint32_t tok = static_cast<uint32_t>(min(n0 + 32 * (t0 + t) + fj, a.N - 1));
+            return __builtin_amdgcn_raw_buffer_load_b128(
+                xrs, 8 * fh < a.T ? tok * static_cast<uint32_t>(2 * a.K) + 48u * a.nblk + 16u * fh : 0x80000000u, 0, 0);
+        };
+        pf_u32x4 at[2] = {};
+        if (tail) at[0] = load_tail(0);
+        float* slot = nullptr;
+        if (S == 2 && !whole)
+            slot = a.partials + static_cast<size_t>(2 * blockIdx.x + (u0 >= base ? 0 : 1)) * kPfSlot + 4 * pf_tid();
 #pragma unroll
-        for (int tg = 0; tg < TG; ++tg)
+        for (int t = 0; t < TH; ++t) {
+            const int tok0 = n0 + 32 * (t0 + t);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[tg][e] = 0.f;
-        for (int v0 = wf; v0 <= wl; v0 += PB) {
-            pf_u32x4 pv[PB][4 * TG];
-#pragma unroll
-            for (int u = 0; u < PB; ++u) {
-                const int v = min(v0 + u, wl);          // past the last: the last again, not added
-                const uint32_t src = pf_slot_bytes(v, v > wf ? 0 : side_wf) + 16u * static_cast<uint32_t>(pf_tid());
-#pragma unroll
-                for (int q = 0; q < 4 * TG; ++q)
-                    pv[u][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, src + 16u * kPfThreads * q, 0, kPfCoherent);
+            for (int e = 0; e < 16; ++e) acc[t][e] *= sg;
+            if (tail) {
+                if (t + 1 < TH) at[(t + 1) & 1] = load_tail(t + 1);
+                acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8_t, at[t & 1]),
+                                                               __builtin_bit_cast(half8_t, bt), acc[t], 0, 0, 0);
             }
+            if (S == 2 && t0 + t >= TG) continue;
+            if (S == 2 && !whole) {
+                // a piece of an item that other workgroups share: slot 0 of the
+                // workgroup for the item where its range starts, slot 1 for the
+                // item where it ends
 #pragma unroll
-            for (int u = 0; u < PB; ++u)
-                if (v0 + u <= wl) {
+                for (int k = 0; k < 4; ++k)
+                    *reinterpret_cast<pf_u32x4*>(slot + 4 * kPfThreads * (4 * t + k)) =
+                        pf_u32x4{pf_bits(acc[t][4 * k]), pf_bits(acc[t][4 * k + 1]), pf_bits(acc[t][4 * k + 2]),
+                                 pf_bits(acc[t][4 * k + 3])};
+                continue;
+            }
+            float* yo = a.y + static_cast<size_t>(tok0) * a.M + row;
 #pragma unroll
-                    for (int tg = 0; tg < TG; ++tg)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e)
-                            acc[tg][e] += pf_float(pf_part(pv[u][4 * tg + (e >> 2)], e & 3));
-                }
+            for (int e = 0; e < 16; ++e) {
+                const int tok = 8 * (e >> 2) + 4 * fh + (e & 3);
+                if (live && tok0 + tok < a.N) yo[static_cast<size_t>(tok) * a.M] = acc[t][e];
+            }
         }
-        if (threadIdx.x == 0) __hip_atomic_store(a.counters + wf, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        finish(acc, wt, live, n0);
     }
+}
+
+// Adds the pieces of the items that several workgroups of gemm_kernel<TG, 2>
+// shared, in workgroup order.  A workgroup takes 256 of an item's quads (four
+// tokens of a row): quad q of thread t of the product's workgroup.
+__global__ __launch_bounds__(256) void gemm_sum_kernel(const GemmArgs a, int tg) {
+    const int item = blockIdx.x;
+    const unsigned long long base = static_cast<unsigned long long>(item) * a.upi;
+    const int wf = pf_worker_of(base, a), wl = pf_worker_of(base + a.upi - 1, a);
+    if (wf == wl) return;
+    const int at = blockIdx.y * 256 + threadIdx.x;         // quad * 512 + thread of the workgroup
+    const int th = (tg + 1) / 2, quad = at / kPfThreads, t = at % kPfThreads;
+    const int wave = t >> 6, h = (t >> 5) & 1, j = t & 31;
+    const int group = (wave & 1) * th + (quad >> 2);
+    const int irow = item / a.tgroups;
+    const int row = (irow * 4 + (wave >> 1)) * 32 + j;
+    const int tok = (item - irow * a.tgroups) * (32 * tg) + 32 * group + 8 * (quad & 3) + 4 * h;
+    if (group >= tg || row >= a.M || tok >= a.N) return;
+    const float4* src = reinterpret_cast<const float4*>(a.partials) + at;
+    const int side = pf_range_begin(wf, a) >= base ? 0 : 1;
+    float4 s = src[static_cast<size_t>(2 * wf + side) * (kPfSlot / 4)];
+    for (int w = wf + 1; w <= wl; w += 4) {
+        float4 p[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) p[u] = src[static_cast<size_t>(2 * min(w + u, wl)) * (kPfSlot / 4)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (w + u <= wl) {
+                s.x += p[u].x;
+                s.y += p[u].y;
+                s.z += p[u].z;
+                s.w += p[u].w;
+            }
+    }
+    float* yo = a.y + static_cast<size_t>(tok) * a.M + row;
+    yo[0] = s.x;
+    if (tok + 1 < a.N) yo[static_cast<size_t>(a.M)] = s.y;
+    if (tok + 2 < a.N) yo[2 * static_cast<size_t>(a.M)] = s.z;
+    if (tok + 3 < a.N) yo[3 * static_cast<size_t>(a.M)] = s.w;
 }
 
 }  // namespace tetra_dev

@@ -29,14 +29,15 @@ using tetra_dev::kTile;
 
 constexpr int kMaxDevices = 64;
 
-// Scratch of tetra_gemm_noalloc: the counters and piece slots of up to
+// Scratch of tetra_gemm_noalloc: the piece slots of up to
 // kScratchWorkers workgroups of the many-token product, the whole chip's
-// worth on a 256-CU part (two workgroups per CU).  Every device holds its own
+// worth on a 256-CU part (one workgroup per CU).  Every device holds its own
 // copy until the process ends; host code reaches it only through the address
 // hipGetSymbolAddress returns for the device (DeviceState::scratch), never
 // through the array's name.
-constexpr int kScratchWorkers = 512;
+constexpr int kScratchWorkers = 256;
 constexpr size_t kScratchBytes = 67110912;   // gemm_workspace_bytes(kScratchWorkers)
+constexpr size_t kMinWorkspace = 131328;     // the smallest workspace tetra_gemm takes
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 
 // What the host knows about a device, queried once and kept: no call makes
@@ -318,6 +319,16 @@ int int4_gemv_launch(const void* q, const uint16_t* scale_off, const uint16_t* x
     return launch_status();
 }
 
+// tetra_dev::gemm_kernel<TG, S> for TG = 1..kPfMaxTG
+template <int S, int TG = 1>
+void gemm_dispatch(int tg, const tetra_dev::GemmArgs& a, hipStream_t stream) {
+    if constexpr (TG <= tetra_dev::kPfMaxTG) {
+        if (tg != TG) return gemm_dispatch<S, TG + 1>(tg, a, stream);
+        hipLaunchKernelGGL((tetra_dev::gemm_kernel<TG, S>), dim3(static_cast<unsigned>(a.workers)),
+                           dim3(tetra_dev::kPfThreads), 0, stream, a);
+    }
+}
+
 }  // namespace
 
 extern "C" {
@@ -483,21 +494,26 @@ int tetra_head4_gemv(const void* q, const uint16_t* scale_off, const uint16_t* x
 
 namespace {
 
-// one launch of the many-token product over tokens n_base .. n_base + N - 1
+// one launch of the many-token product over N tokens; `cus` workgroups fill
+// the chip, `max_workers` of them have piece slots in the workspace
 int gemm_launch(const uint8_t* codes, const uint16_t* row_scales, const uint16_t* x, float* y, int M, int K, int N,
-                const Shape& s, int max_workers, uint8_t* workspace, hipStream_t stream) {
-    const long long token_groups = (static_cast<long long>(N) + tetra_dev::kPfTokens - 1) / tetra_dev::kPfTokens;
-    // four token groups per wave (items of two tiles) unless that cuts the
-    // average item into more than eight pieces over the launch's workgroups;
-    // then two (items of one tile)
+                const Shape& s, int cus, int max_workers, uint8_t* workspace, hipStream_t stream) {
+    // token tiles of up to eight 32-token groups, all of (nearly) one size
+    const long long groups = (static_cast<long long>(N) + 31) / 32;
+    const long long most = (groups + tetra_dev::kPfMaxTG - 1) / tetra_dev::kPfMaxTG;
+    const int tg = static_cast<int>((groups + most - 1) / most);
+    const long long token_tiles = (groups + tg - 1) / tg;
     const int upi = s.nblk / tetra::kGroupCols + (s.nblk % tetra::kGroupCols ? 1 : 0);
-    long long items = static_cast<long long>((s.tiles + 1) / 2) * token_groups;
-    int tg = 4;
-    if (std::min<long long>(items * upi, max_workers) > 8 * items) {
-        tg = 2;
-        items = static_cast<long long>(s.tiles) * token_groups;
-    }
-    if (items >= (1ll << 31)) return TETRA_EINVAL;
+    const long long whole = static_cast<long long>((s.tiles + 3) / 4) * token_tiles;     // S = 1: items of 256 rows
+    const long long halves = static_cast<long long>((s.tiles + 1) / 2) * token_tiles;    // S = 2: of 128 rows
+    if (halves >= (1ll << 31)) return TETRA_EINVAL;
+    // S = 1 takes rounds of `cus` whole items; S = 2 spreads the chunks evenly
+    // but stages the activations twice as often and adds pieces.  Measured:
+    // rounds 3/4 full, 12288 x 4096 by 1024 tokens, 136 us against 146; 5/8
+    // full, 5120 x 5120 by 2048, 157 against 155; 3/8, 12288 x 4096 by 512,
+    // 120 against 88
+    const long long rounds = (whole + cus - 1) / cus;
+    const bool split = max_workers > 0 && 3 * whole < 2 * rounds * cus;
     tetra_dev::GemmArgs a;
     a.codes = codes;
     a.sigma = row_scales;
@@ -511,26 +527,48 @@ int gemm_launch(const uint8_t* codes, const uint16_t* row_scales, const uint16_t
     a.T = s.T;
     a.ng = s.nblk / tetra::kGroupCols;
     a.rem = s.nblk % tetra::kGroupCols;
-    a.tgroups = static_cast<int>(token_groups);
+    a.tgroups = static_cast<int>(token_tiles);
     a.tiles = s.tiles;
     a.upi = upi;
-    a.units = static_cast<unsigned long long>(items) * static_cast<unsigned long long>(a.upi);
+    a.items = static_cast<int>(split ? halves : whole);
+    a.units = static_cast<unsigned long long>(a.items) * static_cast<unsigned long long>(a.upi);
     // at most eight workgroups per item on average: past that, a few more
-    // chunks per workgroup cost less than the longer reduction
-    a.workers = static_cast<int>(std::min<unsigned long long>(
-        std::min<unsigned long long>(a.units, static_cast<unsigned long long>(max_workers)),
-        static_cast<unsigned long long>(items) * 8));
+    // chunks per workgroup cost less than the longer sums (1024 x 5120 by 203
+    // tokens: 28.4, 21.7, 22.2 and 27.8 us with 4, 8, 16 and 32)
+    a.workers = split ? static_cast<int>(std::min<unsigned long long>(
+                            std::min<unsigned long long>(a.units, static_cast<unsigned long long>(max_workers)),
+                            static_cast<unsigned long long>(a.items) * 8))
+                      : static_cast<int>(std::min<long long>(whole, cus));
     if (a.units > ~0ull / static_cast<unsigned long long>(a.workers + 1)) return TETRA_EINVAL;   // range arithmetic
-    a.counters = reinterpret_cast<uint32_t*>(workspace);
-    a.partials = reinterpret_cast<float*>(workspace + tetra_dev::gemm_counter_bytes(max_workers));
-    a.partial_bytes = static_cast<int>(sizeof(float) * 2 * tetra_dev::kPfSlot * static_cast<size_t>(max_workers));
-    if (tg == 4)
-        hipLaunchKernelGGL(tetra_dev::gemm_kernel<4>, dim3(static_cast<unsigned>(a.workers)),
-                           dim3(tetra_dev::kPfThreads), 0, stream, a);
-    else
-        hipLaunchKernelGGL(tetra_dev::gemm_kernel<2>, dim3(static_cast<unsigned>(a.workers)),
-                           dim3(tetra_dev::kPfThreads), 0, stream, a);
+    a.partials = reinterpret_cast<float*>(workspace + tetra_dev::gemm_header_bytes(max_workers));
+    if (!split) {
+        gemm_dispatch<1>(tg, a, stream);
+        return launch_status();
+    }
+    gemm_dispatch<2>(tg, a, stream);
+    if (int st = launch_status()) return st;
+    if (a.units % a.workers == 0 && (a.units / a.workers) % a.upi == 0) return TETRA_OK;   // whole items only
+    hipLaunchKernelGGL(tetra_dev::gemm_sum_kernel,
+                       dim3(static_cast<unsigned>(a.items), static_cast<unsigned>((tg + 1) / 2 * 8)), dim3(256), 0, stream,
+                       a, tg);
     return launch_status();
+}
+
+// a prompt of N tokens: the kernel addresses a launch's activations with
+// 32-bit byte offsets, so prompts longer than that run as several launches of
+// whole token tiles
+int gemm_slices(const void* codes, const uint16_t* row_scales, const uint16_t* x, float* y, int M, int K, int N,
+                const Shape& s, int cus, int max_workers, uint8_t* workspace, hipStream_t stream) {
+    const long long most = 0x7FFFFFFFll / (2ll * K);
+    const long long tile = most >= 32 * tetra_dev::kPfMaxTG ? 32 * tetra_dev::kPfMaxTG : 32;
+    const long long slice = std::max<long long>(tile, most / tile * tile);
+    for (long long n = 0; n < N; n += slice) {
+        const int cnt = static_cast<int>(std::min<long long>(slice, N - n));
+        if (int st = gemm_launch(static_cast<const uint8_t*>(codes), row_scales, x + n * K, y + n * M, M, K, cnt, s, cus,
+                                 max_workers, workspace, stream))
+            return st;
+    }
+    return TETRA_OK;
 }
 
 }  // namespace
@@ -553,33 +591,14 @@ int tetra_gemm(const void* codes, const uint16_t* row_scales, const uint16_t* x,
     if (int st = device_state(&dev, &ds)) return st;
     Shape s;
     if (!shape_of(M, K, &s)) return TETRA_EINVAL;
-    // as many workgroups as the device holds and the workspace has slots for
+    // piece slots for as many workgroups as the device holds and the workspace
+    // has room for; a workspace too small for one runs whole items only
+    if (workspace_bytes < kMinWorkspace) return TETRA_EINVAL;
     int workers = ds.gemm_workers;
     while (workers > 0 && tetra_dev::gemm_workspace_bytes(workers) > workspace_bytes) --workers;
-    if (workers < 1) return TETRA_EINVAL;
-    // the kernel addresses a launch's activations with 32-bit byte offsets:
-    // prompts longer than that run as several launches of whole token groups
-    const long long slice = std::max<long long>(
-        tetra_dev::kPfTokens,
-        ((0x7FFFFFFFll / (2ll * K)) / tetra_dev::kPfTokens) * tetra_dev::kPfTokens);
-    for (long long n = 0; n < N; n += slice) {
-        const int cnt = static_cast<int>(std::min<long long>(slice, N - n));
-        if (int st = gemm_launch(static_cast<const uint8_t*>(codes), row_scales, x + n * K, y + n * M, M, K, cnt, s,
-                                 workers, static_cast<uint8_t*>(workspace), stream))
-            return st;
-    }
-    return TETRA_OK;
+    return gemm_slices(codes, row_scales, x, y, M, K, N, s, ds.gemm_workers, workers, static_cast<uint8_t*>(workspace),
+                       stream);
 }
-
-namespace tetra_dev {
-
-// zeroes n 32-bit words (the counters of a scratch region), so that clearing
-// is a kernel node, not a memset, when the caller captures a graph
-__global__ __launch_bounds__(256) void zero_words_kernel(uint32_t* p, int n) {
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) p[i] = 0u;
-}
-
-}  // namespace tetra_dev
 
 int tetra_gemm_noalloc(const void* codes, const uint16_t* row_scales, const uint16_t* x, float* y, int M, int K,
                        int N, hipStream_t stream) {
@@ -587,7 +606,7 @@ int tetra_gemm_noalloc(const void* codes, const uint16_t* row_scales, const uint
     static_assert(tetra_dev::kMaxGroup == TETRA_MAX_GROUP && tetra_dev::kMaxPhases == TETRA_MAX_PHASES,
                   "limits of the boundary");
     static_assert(sizeof(tetra_dev::GemvChain) <= 4096, "kernel arguments");
-    static_assert(kScratchBytes >= (sizeof(uint32_t) * kScratchWorkers + 255) / 256 * 256 +
+    static_assert(kScratchBytes >= (8 * kScratchWorkers + 255) / 256 * 256 +
                                        sizeof(float) * static_cast<size_t>(kScratchWorkers) * 2 * tetra_dev::kPfSlot,
                   "scratch holds the counters and pieces of kScratchWorkers workgroups");
     if (!codes || !row_scales || !x || !y || M < 1 || K < 24 || N < 1 || K % 8) return TETRA_EINVAL;
@@ -604,21 +623,7 @@ int tetra_gemm_noalloc(const void* codes, const uint16_t* row_scales, const uint
     if (workers < 1) return TETRA_EDEVICE;
     if (workers > kScratchWorkers || tetra_dev::gemm_workspace_bytes(workers) > kScratchBytes)
         return TETRA_EUNSUPPORTED;
-    uint8_t* ws = ds.scratch;
-    const int nctr = static_cast<int>(tetra_dev::gemm_counter_bytes(workers) / sizeof(uint32_t));
-    hipLaunchKernelGGL(tetra_dev::zero_words_kernel, dim3(static_cast<unsigned>((nctr + 255) / 256)), dim3(256), 0,
-                       stream, reinterpret_cast<uint32_t*>(ws), nctr);
-    if (int st = launch_status()) return st;
-    const long long slice = std::max<long long>(
-        tetra_dev::kPfTokens,
-        ((0x7FFFFFFFll / (2ll * K)) / tetra_dev::kPfTokens) * tetra_dev::kPfTokens);
-    for (long long n = 0; n < N; n += slice) {
-        const int cnt = static_cast<int>(std::min<long long>(slice, N - n));
-        if (int st = gemm_launch(static_cast<const uint8_t*>(codes), row_scales, x + n * K, y + n * M, M, K, cnt, s,
-                                 workers, ws, stream))
-            return st;
-    }
-    return TETRA_OK;
+    return gemm_slices(codes, row_scales, x, y, M, K, N, s, workers, workers, ds.scratch, stream);
 }
 
 int tetra_release_stream(hipStream_t stream) {

@@ -86,6 +86,9 @@ __host__ __device__ inline DeviceWord device_word(uint64_t canonical) {
     return d;
 }
 
+// 32-bit and 16-bit parts of the canonical word 0 (the origin)
+constexpr uint32_t kZeroLo = kMidOffset << 13, kZeroHi = kMidOffset << 4;
+
 __host__ __device__ inline uint64_t canonical_from_device(DeviceWord d) {
     CanonicalFields f;
     const uint32_t path = d.lo & 0xFFFu;

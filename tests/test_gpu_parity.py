@@ -986,6 +986,30 @@ def test_gemm_split_items_repeat_bitwise(M, K, N):
     assert torch.equal(y, y2)
 
 
+@pytest.mark.parametrize("ws_bytes", [131328, 256 + 3 * 262144, None])
+@pytest.mark.parametrize("M,K,N", [(129, 24, 32), (257, 192, 65), (65, 96 + 16, 97), (640, 480, 160), (511, 1536, 192),
+                                   (2100, 200, 224), (70, 88, 256), (300, 2400, 257)])
+def test_gemm_token_groups_rows_and_workspaces(M, K, N, ws_bytes):
+    """Every count of 32-token groups in a token tile (1 to 8, and two tiles of
+    five), row counts around the 128 and 256 rows of an item, one to four
+    trailing block columns with and without a tail, a trailing chunk alone
+    (24 and 88 columns); a workspace too small for any piece (whole items),
+    for three workgroups' pieces, and the full one; its contents do not
+    matter."""
+    words, sigma, tail = workloads.tetra_matrix(workloads.seed_for(0, 12) + M + N, M, K)
+    pk = Packed(words, sigma, tail, K)
+    x = workloads.activations(M + N, N, K)
+    ws = torch.full((ws_bytes or tt.gemm_workspace_bytes(),), 0xA5, dtype=torch.uint8, device="cuda")
+    y = torch.full((N, M), float("nan"), dtype=torch.float32, device="cuda")
+    tt.gemm(pk.blob, pk.sigma, _f16_dev(x), y, M, K, N, ws)
+    torch.cuda.synchronize()
+    rows = _sample_rows(M, np.random.default_rng(N), n=64)
+    ref, norm = ogemv.gemv_f64(words[rows], sigma[rows], tail[rows], x)
+    worst = float((np.abs(y.cpu().numpy()[:, rows].astype(np.float64) - ref) / norm).max())
+    print(f"[gemm groups] M={M} K={K} N={N} ws={ws_bytes} worst={worst:.3e}", flush=True)
+    assert torch.isfinite(y).all() and worst <= TOL_GEMM
+
+
 # ----------------------------------------------------------------- encoder
 
 from oracle import codec as ocodec, encoder as oencoder, tables as otables  # noqa: E402
