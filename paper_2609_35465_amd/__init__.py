@@ -72,8 +72,14 @@ def library():
     return _lib
 
 
+_functions = {}                    # by name, bound at their first call
+
+
 def _call(name, *args):
-    return getattr(library(), name)(*args)
+    f = _functions.get(name)
+    if f is None:
+        f = _functions[name] = getattr(library(), name)
+    return f(*args)
 
 
 class TetraError(RuntimeError):
@@ -138,11 +144,28 @@ def unpack_rows(codes: np.ndarray, M: int, K: int):
 
 # ---------------------------------------------------------------- device side
 
+_device, _raw_stream = None, None  # torch's own getters behind current_stream(), once torch.cuda is up
+
+
 def _stream(stream):
+    """The stream to launch on: the caller's, or torch's current one.  Asked
+    for as an integer: torch.cuda.current_stream() builds a stream object
+    around it on every call, which cost more than the launch's arguments."""
     if stream is not None:
         return stream
+    if _raw_stream is not None:
+        return _raw_stream(_device())
+    return _first_stream()
+
+
+def _first_stream():
+    global _device, _raw_stream
     import torch
-    return torch.cuda.current_stream().cuda_stream
+    raw = torch.cuda.current_stream().cuda_stream       # initialises torch.cuda
+    device, get = getattr(torch._C, "_cuda_getDevice", None), getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if device is not None and get is not None:
+        _device, _raw_stream = device, get
+    return raw
 
 
 def _ptr(t):
