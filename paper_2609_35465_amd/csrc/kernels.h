@@ -440,6 +440,21 @@ inline int gemv_waves(uint32_t total, int cus, int groups) {
     return static_cast<int>(want < cap ? want : cap);
 }
 
+// Whether a single-phase launch whose tiles all have nblk block columns gives
+// every tile a workgroup of its own (waves = 12 per tile): its pieces then
+// meet in LDS alone, which saves the sums' device-wide round trips (store,
+// count, load), 1-2 us.  Up to one workgroup per CU, with a block for every
+// wave, and up to 112 columns, about nine per wave: beyond, the longer pieces
+// cost more than that.  Measured over graph replays, even split against this
+// one: 1536 x 1536 (64 columns) 8.4 -> 7.0 us at batch 1, 9.6 -> 7.7 at 2,
+// 11.4 -> 9.6 at 8; 4096 x 2560 (106) 9.9 -> 8.9, 11.3 -> 10.1, 14.7 -> 14.1;
+// 16384 x 2560 (256 tiles) 14.0 -> 9.5 at batch 1; 1024 x 5120 (213 columns)
+// 9.6 -> 11.7; 17408 x 1024 (272 tiles, 42 columns) 9.6 -> 10.1.
+constexpr int kGemvTileColumns = 112;
+inline bool gemv_tile_per_group(int nblk, uint32_t tiles, int cus) {
+    return nblk >= kGemvWaves && nblk <= kGemvTileColumns && tiles <= static_cast<uint32_t>(cus);
+}
+
 // Waves per workgroup in one phase of a chain: its launch holds a whole
 // round of workgroups anyway, and the tables are staged once for all phases,
 // so a wave is worth fewer blocks than in a single launch (at least
@@ -1611,18 +1626,27 @@ __device__ __forceinline__ void finish_piece(const GemvProblem& P, const GemvSpl
                                          __HIP_MEMORY_SCOPE_WORKGROUP);
     arrived = __builtin_amdgcn_readfirstlane(arrived);
     if (arrived != static_cast<uint32_t>(b - a)) return;
-    // last of this workgroup's pieces of the tile: add them in wave order
+    // last of this workgroup's pieces of the tile: add them in wave order, every
+    // other one apart (two shorter chains round less than one: with twelve
+    // pieces of five blocks 8.9e-8 of the result against 8.3e-8)
     const bool inside = wa >= w0 && wb <= wlast;   // the tile lies in this workgroup
     RowTail rt;
     if (inside) rt = load_rows(P, t);   // in flight while the sums combine
-    float tot[B];
+    float tot[B], odd[B];
 #pragma unroll
-    for (int bb = 0; bb < B; ++bb) tot[bb] = 0.f;
-    for (int v = a; v <= b; ++v) {
+    for (int bb = 0; bb < B; ++bb) tot[bb] = odd[bb] = 0.f;
+    for (int v = a; v <= b; v += 2) {
         const float* pv = s_piece + ((v - w0) * 2 + slot_of(v)) * B * 64 + ln;
 #pragma unroll
         for (int bb = 0; bb < B; ++bb) tot[bb] += pv[bb * 64];
+        if (v < b) {
+            const float* po = s_piece + ((v + 1 - w0) * 2) * B * 64 + ln;   // slot 0: past the first contributor
+#pragma unroll
+            for (int bb = 0; bb < B; ++bb) odd[bb] += po[bb * 64];
+        }
     }
+#pragma unroll
+    for (int bb = 0; bb < B; ++bb) tot[bb] += odd[bb];
     if (inside) {
         store_rows<B>(P, t, tot, rt);
         return;

@@ -214,7 +214,12 @@ int launch_gemv(const tetra_gemv_problem* probs, int n, const int* counts, int n
                           tetra_dev::kGemvWaves;
     int grid;
     if (n_phases == 1) {
-        ch.ph[0].waves = std::min(tetra_dev::gemv_waves(ch.ph[0].total, cus, ds.gemv_groups[batch]), max_waves);
+        const int nblk = ch.prob[0].nblk;
+        const bool one_width = std::all_of(ch.prob, ch.prob + n, [&](const tetra_dev::GemvProblem& P) { return P.nblk == nblk; });
+        ch.ph[0].waves = std::min(one_width && tetra_dev::gemv_tile_per_group(nblk, ch.ph[0].total / nblk, cus)
+                                      ? static_cast<int>(ch.ph[0].total / nblk) * tetra_dev::kGemvWaves
+                                      : tetra_dev::gemv_waves(ch.ph[0].total, cus, ds.gemv_groups[batch]),
+                                  max_waves);
         ch.ph[0].wpg = tetra_dev::kGemvWaves;
         grid = (ch.ph[0].waves + tetra_dev::kGemvWaves - 1) / tetra_dev::kGemvWaves;
     } else {

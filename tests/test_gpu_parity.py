@@ -592,6 +592,25 @@ def test_gemv_config_every_row(config, batch, idx):
 
 # ------------------------------------------------------------- determinism
 
+@pytest.mark.parametrize("batch", [1, 2, 3, 8])
+@pytest.mark.parametrize("M,K", [(64, 24 * 11 + 2), (64, 24 * 12), (200, 24 * 13 + 4), (100, 24 * 112 + 22),
+                                 (100, 24 * 113), (64 * 256, 24 * 12), (64 * 256 + 1, 24 * 12 + 6)])
+def test_gemv_tile_per_workgroup_edges(M, K, batch):
+    """Widths and tile counts around the launches that give every tile a
+    workgroup of its own (12 to 112 block columns, up to 256 tiles): sampled
+    rows against the oracle, two calls with the same bits."""
+    words, sigma, tail = workloads.tetra_matrix(workloads.seed_for(0, 13) + M + K, M, K)
+    pk = Packed(words, sigma, tail, K)
+    x = workloads.activations(M + K + batch, batch, K)
+    y = pk.gemv(x)
+    rows = np.unique(np.concatenate([_sample_rows(M, np.random.default_rng(K), n=96), [M - 1]]))
+    ref, norm = ogemv.gemv_f64(words[rows], sigma[rows], tail[rows], x)
+    worst = float((np.abs(y[:, rows].astype(np.float64) - ref) / norm).max())
+    print(f"[gemv tile groups] M={M} K={K} batch={batch} worst={worst:.3e}", flush=True)
+    assert worst <= TOL_PAPER
+    assert np.array_equal(pk.gemv(x), y)
+
+
 def test_gemv_repeat_is_bitwise_identical():
     """Pieces of row tiles are added in a fixed order: repeated launches give
     the same bits (tiles here are split over many waves and workgroups)."""
