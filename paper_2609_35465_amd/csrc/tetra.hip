@@ -672,20 +672,16 @@ int tetra_rotate(const uint16_t* x, const uint8_t* sign_bits, uint16_t* out, int
     DeviceState ds;
     if (int st = device_state(&dev, &ds)) return st;
     const float scale = static_cast<float>(1.0 / std::sqrt(static_cast<double>(n)));
-    const int T = n <= 1024 ? 256 : n / 4;
-    const dim3 grid(static_cast<unsigned>((K + 4 * T - 1) / (4 * T)), static_cast<unsigned>(rows));
-    switch (T) {
-        case 256:
-            hipLaunchKernelGGL(tetra_dev::rotate_kernel<256>, grid, dim3(256), 0, stream, x, sign_bits, out, K, n, scale);
-            break;
-        case 512:
-            hipLaunchKernelGGL(tetra_dev::rotate_kernel<512>, grid, dim3(512), 0, stream, x, sign_bits, out, K, n, scale);
-            break;
-        default:
-            hipLaunchKernelGGL(tetra_dev::rotate_kernel<1024>, grid, dim3(1024), 0, stream, x, sign_bits, out, K, n,
-                               scale);
-            break;
-    }
+    const long long group = 512ll * (n <= 512 ? 1 : 2) * tetra_dev::kRotWaves;     // elements of a workgroup
+    const dim3 grid(static_cast<unsigned>((K + group - 1) / group), static_cast<unsigned>(rows));
+    const dim3 block(tetra_dev::kRotWaves * 64);
+#define TETRA_ROTATE(G, W) \
+    hipLaunchKernelGGL((tetra_dev::rotate_kernel<G, W>), grid, block, 0, stream, x, sign_bits, out, K, n, scale)
+    if (n <= 512) TETRA_ROTATE(1, 1);
+    else if (n == 1024) TETRA_ROTATE(2, 1);
+    else if (n == 2048) TETRA_ROTATE(2, 2);
+    else TETRA_ROTATE(2, 4);
+#undef TETRA_ROTATE
     return launch_status();
 }
 
