@@ -1956,19 +1956,23 @@ __device__ __forceinline__ void int4_load_w(Int4W& a, const uint8_t* __restrict_
     }
 }
 
+// a row's 16 nibbles as fp16 pairs (1024 + q_e, 1024 + q_{e+4})
+__device__ __forceinline__ void int4_pairs(uint32_t (&np)[8], uint2 w) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t d = h ? w.y : w.x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) np[4 * h + e] = ((d >> (4 * e)) & 0x000F000Fu) | 0x64006400u;
+    }
+}
+
 template <int B>
 __device__ __forceinline__ void int4_step(float (&acc)[kInt4RowsPerWave][B], const Int4W& a, const Int4X<B>& xa) {
 #pragma unroll
     for (int r = 0; r < kInt4RowsPerWave; ++r) {
         const float sc = f16(static_cast<uint16_t>(a.so[r])), of = f16(static_cast<uint16_t>(a.so[r] >> 16));
         uint32_t np[8];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint32_t d = h ? a.w[r].y : a.w[r].x;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                np[4 * h + e] = ((d >> (4 * e)) & 0x000F000Fu) | 0x64006400u;   // (1024 + q_e, 1024 + q_{e+4})
-        }
+        int4_pairs(np, a.w[r]);
 #pragma unroll
         for (int bb = 0; bb < B; ++bb) {
             float dt = 0.f;
@@ -2026,7 +2030,6 @@ __global__ __launch_bounds__(kInt4Waves * 64) void int4_gemv_kernel(const uint8_
 
 constexpr int kInt4LdsWaves = 16;
 constexpr int kInt4LdsThreads = kInt4LdsWaves * 64;
-constexpr int kInt4LdsMaxBatch = 5;    // larger batches would spill at four waves per SIMD
 
 // workgroups per CU of the persistent kernel: two at batch 1 (64 VGPRs),
 // one above
@@ -2087,12 +2090,40 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
                     a.sx[bb] = s_sx[bb * chunks + k / 16];
                 }
             };
-            // each step's activations just before the step (one register set)
-            lds_x(xa, k0);
-            int4_step<B>(acc, wa, xa);
-            if (two) {
-                lds_x(xa, k1);
-                int4_step<B>(acc, wb, xa);
+            // from batch 6 on the activations of all rows at once would spill:
+            // two batch rows at a time, against both rows' pairs (the same sums)
+            auto step_by_two = [&](const Int4W& w, int k) {
+                uint32_t np[kInt4RowsPerWave][8];
+#pragma unroll
+                for (int r = 0; r < kInt4RowsPerWave; ++r) int4_pairs(np[r], w.w[r]);
+#pragma unroll
+                for (int bb = 0; bb < B; ++bb) {
+                    const uint4* sp = reinterpret_cast<const uint4*>(s_xp + (static_cast<size_t>(bb) * chunks + k / 16) * 8);
+                    const uint4 u = sp[0], v = sp[1];
+                    const uint32_t xp[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+                    const float sx = s_sx[bb * chunks + k / 16];
+#pragma unroll
+                    for (int r = 0; r < kInt4RowsPerWave; ++r) {
+                        const float sc = f16(static_cast<uint16_t>(w.so[r])), of = f16(static_cast<uint16_t>(w.so[r] >> 16));
+                        float dt = 0.f;
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) dt = dot2(np[r][i], xp[i], dt);
+                        acc[r][bb] = fmaf(sc, fmaf(-1024.f, sx, dt), fmaf(of, sx, acc[r][bb]));
+                    }
+                    if (bb & 1) __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            if constexpr (B >= 6) {
+                step_by_two(wa, k0);
+                if (two) step_by_two(wb, k1);
+            } else {
+                // each step's activations just before the step (one register set)
+                lds_x(xa, k0);
+                int4_step<B>(acc, wa, xa);
+                if (two) {
+                    lds_x(xa, k1);
+                    int4_step<B>(acc, wb, xa);
+                }
             }
         }
 #pragma unroll

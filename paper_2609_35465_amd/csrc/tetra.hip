@@ -298,20 +298,20 @@ int int4_gemv_launch(const void* q, const uint16_t* scale_off, const uint16_t* x
     if (grid > 0x7FFFFFFFLL) return TETRA_EINVAL;
     const uint8_t* qb = static_cast<const uint8_t*>(q);
     // a launch of at least one row pair per wave of a full chip of persistent
-    // workgroups stages the activations in LDS (when they fit in 64 KB)
+    // workgroups stages the activations in LDS, when they fit: in 64 KB up to
+    // batch 5 (10,000 x 9,600 at batch 5, 105 KB: 33.4 us without, 35.9 with),
+    // in 128 KB from batch 6 on, where the per-row-pair kernel is slow
+    // (151,936 x 5,120 at batch 8, 90 KB: 459 us without, 258 with; 17,408 x
+    // 5,120: 53.9 and 42.9; 10,000 x 9,600 at batch 6, 127 KB: 43.3 and 40.9)
     const long long lds_groups = static_cast<long long>(tetra_dev::int4_lds_groups_per_cu(batch)) * ds.cus;
     const size_t lds = tetra_dev::int4_lds_bytes(K, batch);
-    const bool use_lds = batch <= tetra_dev::kInt4LdsMaxBatch &&
-                         pairs >= lds_groups * tetra_dev::kInt4LdsWaves && lds <= 65536;
+    const bool use_lds = pairs >= lds_groups * tetra_dev::kInt4LdsWaves && lds <= (batch <= 5 ? 65536u : 131072u);
 #define TETRA_I4(B)                                                                                          \
     case B:                                                                                                  \
-        if constexpr (B <= tetra_dev::kInt4LdsMaxBatch) {                                                    \
-            if (use_lds) {                                                                                   \
-                hipLaunchKernelGGL((tetra_dev::int4_gemv_lds_kernel<B, G>),                                  \
-                                   dim3(static_cast<unsigned>(lds_groups)), dim3(tetra_dev::kInt4LdsThreads), \
-                                   lds, stream, qb, scale_off, x, y, M, K);                                  \
-                break;                                                                                       \
-            }                                                                                                \
+        if (use_lds) {                                                                                       \
+            hipLaunchKernelGGL((tetra_dev::int4_gemv_lds_kernel<B, G>), dim3(static_cast<unsigned>(lds_groups)), \
+                               dim3(tetra_dev::kInt4LdsThreads), lds, stream, qb, scale_off, x, y, M, K);    \
+            break;                                                                                           \
         }                                                                                                    \
         hipLaunchKernelGGL((tetra_dev::int4_gemv_kernel<B, G>), dim3(static_cast<unsigned>(grid)),           \
                            dim3(tetra_dev::kInt4Waves * 64), 0, stream, qb, scale_off, x, y, M, K);          \

@@ -776,6 +776,27 @@ def test_head4_gemv_full_size_sampled():
 
 # ------------------------------------------------------------------- emb4
 
+@pytest.mark.parametrize("batch", [2, 5, 6, 7, 8])
+@pytest.mark.parametrize("M,K", [(8191, 1152), (8192, 1024), (8194, 7296)])
+def test_int4_wide_batches_staged_bits(M, K, batch):
+    """Launches on either side of the row count from which the activations are
+    staged in LDS (8,192 rows on 256 CUs; up to 128 KB of them, which K = 7,296
+    at batch 8 passes): the bits of the per-row-pair kernel on slices of the
+    rows, for every batch row."""
+    q, so = workloads.int4_matrix(M + K, M, K)
+    x = workloads.activations(M + batch, batch, K)
+    qd, sd, xd = _dev(q), _f16_dev(so), _f16_dev(x)
+    y = torch.full((batch, M), float("nan"), dtype=torch.float32, device="cuda")
+    tt.int4_gemv(qd, sd, xd, y, M, K, batch)
+    for r0 in (0, 3002, M - 1501):
+        m = min(1501, M - r0)
+        part = torch.full((batch, m), float("nan"), dtype=torch.float32, device="cuda")
+        tt.int4_gemv(qd[r0:r0 + m].contiguous(), sd[r0:r0 + m].contiguous(), xd, part, m, K, batch)
+        torch.cuda.synchronize()
+        assert torch.equal(part, y[:, r0:r0 + m]), (M, K, batch, r0)
+    print(f"[int4 staged] M={M} K={K} batch={batch} ok", flush=True)
+
+
 def test_emb4_gather_bit_exact():
     rows, dim = 3000, 5120
     q, so, token = workloads.emb4_table(5, rows, dim)
