@@ -2026,7 +2026,12 @@ __global__ __launch_bounds__(kInt4Waves * 64) void int4_gemv_kernel(const uint8_
 // and 16-weight chunk: the eight permuted fp16 pairs and the chunk's sum), so
 // that the steps read them from LDS instead of fetching the vector from L2
 // for every pair of rows (that traffic was twice the weight stream).  Each
-// wave then takes row pairs rg, rg + waves, ... of the launch.
+// wave then takes row pairs rg, rg + waves, ... of the launch.  At batch 1 the
+// pairs past the last whole round are shared out by steps of 1,024 columns,
+// requested before all else and added at the end in the order of the steps (a
+// round of 512 pairs of 8,192 waves cost as long a chain of loads as a full
+// one): 17,408 x 5,120 12.06 -> 11.44 us (3.9 -> 4.2 TB/s), a table of 151,936
+// rows the same (82.1 and 82.3 us).
 
 constexpr int kInt4LdsWaves = 16;
 constexpr int kInt4LdsThreads = kInt4LdsWaves * 64;
@@ -2041,6 +2046,9 @@ __host__ __device__ constexpr size_t int4_lds_bytes(int K, int B) {
     return static_cast<size_t>(B) * (K / 16) * (8 * 4 + 4);
 }
 
+// LDS bytes after them, at batch 1: each wave's step of a shared row pair
+inline size_t int4_rest_bytes(int B) { return B == 1 ? kInt4LdsThreads * sizeof(uint4) : 0; }
+
 template <int B, int G>
 __global__ __launch_bounds__(kInt4LdsThreads) __attribute__((amdgpu_waves_per_eu(B == 1 ? 8 : 4)))
 void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
@@ -2051,9 +2059,24 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
     uint32_t* s_xp = reinterpret_cast<uint32_t*>(s_x4);                 // [B][K/16][8]
     const int chunks = K / 16;
     float* s_sx = reinterpret_cast<float*>(s_xp + static_cast<size_t>(B) * chunks * 8);   // [B][K/16]
-    for (int c = threadIdx.x; c < chunks; c += kInt4LdsThreads) {
-        Int4X<B> a;
-        int4_load_x<B>(a, x, K, 16 * c);
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int pairs = (M + kInt4RowsPerWave - 1) / kInt4RowsPerWave;
+    const int waves = gridDim.x * kInt4LdsWaves;
+    const int rg0 = blockIdx.x * kInt4LdsWaves + wave;
+    const int first_k = 16 * lane;
+
+    // The row pairs past the last whole round, when a workgroup's share of
+    // them has at most as many steps as it has waves: shared out by steps
+    [[maybe_unused]] const int steps = (K + 1023) / 1024;
+    const int whole = pairs / waves * waves;
+    const int share = (pairs - whole + static_cast<int>(gridDim.x) - 1) / static_cast<int>(gridDim.x);
+    const bool by_steps = B == 1 && share * steps <= kInt4LdsWaves;
+    [[maybe_unused]] const int rest_pair = whole + wave / steps * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x);
+    [[maybe_unused]] const int rest_k = first_k + 1024 * (wave % steps);
+    [[maybe_unused]] const bool has_rest = by_steps && wave / steps < share && rest_pair < pairs && rest_k < K;
+
+    auto stage = [&](const Int4X<B>& a, int c) {
 #pragma unroll
         for (int bb = 0; bb < B; ++bb) {
             uint4* d = reinterpret_cast<uint4*>(s_xp + (static_cast<size_t>(bb) * chunks + c) * 8);
@@ -2061,71 +2084,119 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
             d[1] = make_uint4(a.xp[bb][4], a.xp[bb][5], a.xp[bb][6], a.xp[bb][7]);
             s_sx[bb * chunks + c] = a.sx[bb];
         }
+    };
+    // Up to batch 5 the wave's first weights are requested behind its
+    // activations and before those are staged, so that both latencies run
+    // together (clamped to the matrix: what lies past its end is not used);
+    // above, the staged rows and the weights at once would spill
+    constexpr bool kEarly = B <= 5;
+    Int4W wa, wb;
+    [[maybe_unused]] Int4W wr;
+    int c = threadIdx.x;
+    if constexpr (kEarly) {
+        Int4X<B> a;
+        int4_load_x<B>(a, x, K, 16 * min(c, chunks - 1));
+        if constexpr (B == 1)
+            int4_load_w<G>(wr, q, so, M, K, (has_rest ? rest_pair : min(rg0, pairs - 1)) * kInt4RowsPerWave,
+                           has_rest ? rest_k : min(first_k, K - 16));
+        int4_load_w<G>(wa, q, so, M, K, min(rg0, pairs - 1) * kInt4RowsPerWave, min(first_k, K - 16));
+        int4_load_w<G>(wb, q, so, M, K, min(rg0, pairs - 1) * kInt4RowsPerWave, min(first_k + 1024, K - 16));
+        if (c < chunks) stage(a, c);
+        c += kInt4LdsThreads;
+    }
+    for (; c < chunks; c += kInt4LdsThreads) {
+        Int4X<B> a;
+        int4_load_x<B>(a, x, K, 16 * c);
+        stage(a, c);
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63;
-    const int pairs = (M + kInt4RowsPerWave - 1) / kInt4RowsPerWave;
-    const int waves = gridDim.x * kInt4LdsWaves;
-    for (int rg = blockIdx.x * kInt4LdsWaves + (threadIdx.x >> 6); rg < pairs; rg += waves) {
-        const int r0 = rg * kInt4RowsPerWave;
-        float acc[kInt4RowsPerWave][B];
+
+    auto lds_x = [&](Int4X<B>& a, int k) {
+#pragma unroll
+        for (int bb = 0; bb < B; ++bb) {
+            const uint4* sp = reinterpret_cast<const uint4*>(s_xp + (static_cast<size_t>(bb) * chunks + k / 16) * 8);
+            const uint4 u = sp[0], v = sp[1];
+            a.xp[bb][0] = u.x; a.xp[bb][1] = u.y; a.xp[bb][2] = u.z; a.xp[bb][3] = u.w;
+            a.xp[bb][4] = v.x; a.xp[bb][5] = v.y; a.xp[bb][6] = v.z; a.xp[bb][7] = v.w;
+            a.sx[bb] = s_sx[bb * chunks + k / 16];
+        }
+    };
+    [[maybe_unused]] uint4* s_rest = reinterpret_cast<uint4*>(s_sx + static_cast<size_t>(B) * chunks);   // [waves][64]
+    if constexpr (B == 1) {
+        // the step's sums of q x, with scale and offset, for the pair's owner
+        if (has_rest) {
+            Int4X<B> xa;
+            lds_x(xa, rest_k);
+            float t[kInt4RowsPerWave];
+#pragma unroll
+            for (int r = 0; r < kInt4RowsPerWave; ++r) {
+                uint32_t np[8];
+                int4_pairs(np, wr.w[r]);
+                float dt = 0.f;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) dt = dot2(np[i], xa.xp[0][i], dt);
+                t[r] = fmaf(-1024.f, xa.sx[0], dt);
+            }
+            s_rest[threadIdx.x] = make_uint4(__builtin_bit_cast(uint32_t, t[0]), wr.so[0],
+                                             __builtin_bit_cast(uint32_t, t[1]), wr.so[1]);
+        }
+    }
+
+    float acc[kInt4RowsPerWave][B];
+    auto clear = [&] {
 #pragma unroll
         for (int r = 0; r < kInt4RowsPerWave; ++r)
 #pragma unroll
             for (int bb = 0; bb < B; ++bb) acc[r][bb] = 0.f;
-        for (int k0 = 16 * lane; k0 < K; k0 += 2048) {
-            const int k1 = k0 + 1024;
-            const bool two = k1 < K;
-            Int4W wa, wb;
+    };
+    // from batch 6 on the activations of all rows at once would spill:
+    // two batch rows at a time, against both rows' pairs (the same sums)
+    auto step_by_two = [&](const Int4W& w, int k) {
+        uint32_t np[kInt4RowsPerWave][8];
+#pragma unroll
+        for (int r = 0; r < kInt4RowsPerWave; ++r) int4_pairs(np[r], w.w[r]);
+#pragma unroll
+        for (int bb = 0; bb < B; ++bb) {
+            const uint4* sp = reinterpret_cast<const uint4*>(s_xp + (static_cast<size_t>(bb) * chunks + k / 16) * 8);
+            const uint4 u = sp[0], v = sp[1];
+            const uint32_t xp[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+            const float sx = s_sx[bb * chunks + k / 16];
+#pragma unroll
+            for (int r = 0; r < kInt4RowsPerWave; ++r) {
+                const float sc = f16(static_cast<uint16_t>(w.so[r])), of = f16(static_cast<uint16_t>(w.so[r] >> 16));
+                float dt = 0.f;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) dt = dot2(np[r][i], xp[i], dt);
+                acc[r][bb] = fmaf(sc, fmaf(-1024.f, sx, dt), fmaf(of, sx, acc[r][bb]));
+            }
+            if (bb & 1) __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto use = [&](const Int4W& a, const Int4W& b, int k0) {
+        const int k1 = k0 + 1024;
+        if constexpr (B >= 6) {
+            step_by_two(a, k0);
+            if (k1 < K) step_by_two(b, k1);
+        } else {
+            // each step's activations just before the step (one register set)
             Int4X<B> xa;
-            int4_load_w<G>(wa, q, so, M, K, r0, k0);
-            if (two) int4_load_w<G>(wb, q, so, M, K, r0, k1);
-            auto lds_x = [&](Int4X<B>& a, int k) {
-#pragma unroll
-                for (int bb = 0; bb < B; ++bb) {
-                    const uint4* sp = reinterpret_cast<const uint4*>(s_xp + (static_cast<size_t>(bb) * chunks + k / 16) * 8);
-                    const uint4 u = sp[0], v = sp[1];
-                    a.xp[bb][0] = u.x; a.xp[bb][1] = u.y; a.xp[bb][2] = u.z; a.xp[bb][3] = u.w;
-                    a.xp[bb][4] = v.x; a.xp[bb][5] = v.y; a.xp[bb][6] = v.z; a.xp[bb][7] = v.w;
-                    a.sx[bb] = s_sx[bb * chunks + k / 16];
-                }
-            };
-            // from batch 6 on the activations of all rows at once would spill:
-            // two batch rows at a time, against both rows' pairs (the same sums)
-            auto step_by_two = [&](const Int4W& w, int k) {
-                uint32_t np[kInt4RowsPerWave][8];
-#pragma unroll
-                for (int r = 0; r < kInt4RowsPerWave; ++r) int4_pairs(np[r], w.w[r]);
-#pragma unroll
-                for (int bb = 0; bb < B; ++bb) {
-                    const uint4* sp = reinterpret_cast<const uint4*>(s_xp + (static_cast<size_t>(bb) * chunks + k / 16) * 8);
-                    const uint4 u = sp[0], v = sp[1];
-                    const uint32_t xp[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
-                    const float sx = s_sx[bb * chunks + k / 16];
-#pragma unroll
-                    for (int r = 0; r < kInt4RowsPerWave; ++r) {
-                        const float sc = f16(static_cast<uint16_t>(w.so[r])), of = f16(static_cast<uint16_t>(w.so[r] >> 16));
-                        float dt = 0.f;
-#pragma unroll
-                        for (int i = 0; i < 8; ++i) dt = dot2(np[r][i], xp[i], dt);
-                        acc[r][bb] = fmaf(sc, fmaf(-1024.f, sx, dt), fmaf(of, sx, acc[r][bb]));
-                    }
-                    if (bb & 1) __builtin_amdgcn_sched_barrier(0);
-                }
-            };
-            if constexpr (B >= 6) {
-                step_by_two(wa, k0);
-                if (two) step_by_two(wb, k1);
-            } else {
-                // each step's activations just before the step (one register set)
-                lds_x(xa, k0);
-                int4_step<B>(acc, wa, xa);
-                if (two) {
-                    lds_x(xa, k1);
-                    int4_step<B>(acc, wb, xa);
-                }
+            lds_x(xa, k0);
+            int4_step<B>(acc, a, xa);
+            if (k1 < K) {
+                lds_x(xa, k1);
+                int4_step<B>(acc, b, xa);
             }
         }
+    };
+    auto walk = [&](int r0, int k_from) {
+        for (int k0 = k_from; k0 < K; k0 += 2048) {
+            const int k1 = k0 + 1024;
+            int4_load_w<G>(wa, q, so, M, K, r0, k0);
+            if (k1 < K) int4_load_w<G>(wb, q, so, M, K, r0, k1);
+            use(wa, wb, k0);
+        }
+    };
+    auto finish = [&](int r0) {
 #pragma unroll
         for (int r = 0; r < kInt4RowsPerWave; ++r)
 #pragma unroll
@@ -2133,6 +2204,37 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
                 const float v = wave_sum(acc[r][bb]);
                 if (lane == 0 && r0 + r < M) y[static_cast<size_t>(bb) * M + r0 + r] = v;
             }
+    };
+    const int end = by_steps ? whole : pairs;
+    int rg = rg0;
+    if (kEarly && rg < end) {
+        clear();
+        if (first_k < K) use(wa, wb, first_k);
+        walk(rg * kInt4RowsPerWave, first_k + 2048);
+        finish(rg * kInt4RowsPerWave);
+        rg += waves;
+    }
+    for (; rg < end; rg += waves) {
+        clear();
+        walk(rg * kInt4RowsPerWave, first_k);
+        finish(rg * kInt4RowsPerWave);
+    }
+    if constexpr (B == 1) {
+        if (!by_steps || share == 0) return;
+        __syncthreads();
+        const int pair = whole + wave * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x);
+        if (wave >= share || pair >= pairs) return;
+        clear();
+        // a lane's steps in the order one wave would have taken them
+        for (int s = 0; first_k + 1024 * s < K; ++s) {
+            const uint4 t = s_rest[(wave * steps + s) * 64 + lane];
+            const float sx = s_sx[(first_k + 1024 * s) / 16];
+            acc[0][0] = fmaf(f16(static_cast<uint16_t>(t.y)), __builtin_bit_cast(float, t.x),
+                             fmaf(f16(static_cast<uint16_t>(t.y >> 16)), sx, acc[0][0]));
+            acc[1][0] = fmaf(f16(static_cast<uint16_t>(t.w)), __builtin_bit_cast(float, t.z),
+                             fmaf(f16(static_cast<uint16_t>(t.w >> 16)), sx, acc[1][0]));
+        }
+        finish(pair * kInt4RowsPerWave);
     }
 }
 

@@ -310,7 +310,7 @@ int int4_gemv_launch(const void* q, const uint16_t* scale_off, const uint16_t* x
     case B:                                                                                                  \
         if (use_lds) {                                                                                       \
             hipLaunchKernelGGL((tetra_dev::int4_gemv_lds_kernel<B, G>), dim3(static_cast<unsigned>(lds_groups)), \
-                               dim3(tetra_dev::kInt4LdsThreads), lds, stream, qb, scale_off, x, y, M, K);    \
+                               dim3(tetra_dev::kInt4LdsThreads), lds + tetra_dev::int4_rest_bytes(B), stream, qb, scale_off, x, y, M, K);    \
             break;                                                                                           \
         }                                                                                                    \
         hipLaunchKernelGGL((tetra_dev::int4_gemv_kernel<B, G>), dim3(static_cast<unsigned>(grid)),           \
