@@ -1944,15 +1944,41 @@ struct Int4W {
     uint32_t so[kInt4RowsPerWave];
 };
 
+// A row pair's buffers: a wave-uniform base and a 32-bit lane offset per load
+// (64-bit lane addresses took 12 VGPRs more), the row's length as the limit, so
+// that a lane past the end of K reads zeros.  The loads were held by issue
+// slots and registers, not by HBM alone: 151,936 x 5,120 at batch 1 82.7 ->
+// 77.1 us (5.30 -> 5.68 TB/s), and batch 2 fits 64 VGPRs.  Three or four steps
+// in flight with the registers freed: 17,408 x 5,120 11.7 and 11.9 us against
+// 11.3 for two.
+struct Int4Rows {
+    __amdgpu_buffer_rsrc_t q[kInt4RowsPerWave], so[kInt4RowsPerWave];
+};
+
 template <int G>
-__device__ __forceinline__ void int4_load_w(Int4W& a, const uint8_t* __restrict__ q, const uint16_t* __restrict__ so,
-                                            int M, int K, int r0, int k0) {
+__device__ __forceinline__ Int4Rows int4_rows(const uint8_t* q, const uint16_t* so, int M, int K, int r0) {
+    constexpr int kRawDword = 0x00020000;          // word 3 of the descriptor: untyped 32-bit data
     const int groups = K / G;
+    Int4Rows b;
 #pragma unroll
     for (int r = 0; r < kInt4RowsPerWave; ++r) {
         const int row = min(r0 + r, M - 1);
-        a.w[r] = *reinterpret_cast<const uint2*>(q + static_cast<size_t>(row) * (K >> 1) + (k0 >> 1));
-        a.so[r] = *reinterpret_cast<const uint32_t*>(so + (static_cast<size_t>(row) * groups + k0 / G) * 2);
+        b.q[r] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(q) + static_cast<size_t>(row) * (K >> 1), 0,
+                                                   K >> 1, kRawDword);
+        b.so[r] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(so) + static_cast<size_t>(row) * groups * 2,
+                                                    0, groups * 4, kRawDword);
+    }
+    return b;
+}
+
+template <int G>
+__device__ __forceinline__ void int4_load_w(Int4W& a, const Int4Rows& b, int k0) {
+    typedef uint32_t pair_t __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int r = 0; r < kInt4RowsPerWave; ++r) {
+        const pair_t w = __builtin_amdgcn_raw_buffer_load_b64(b.q[r], k0 >> 1, 0, 0);
+        a.w[r] = make_uint2(w.x, w.y);
+        a.so[r] = __builtin_amdgcn_raw_buffer_load_b32(b.so[r], static_cast<uint32_t>(k0) / G * 4, 0, 0);
     }
 }
 
@@ -1990,9 +2016,10 @@ __global__ __launch_bounds__(kInt4Waves * 64) void int4_gemv_kernel(const uint8_
                                                                    const uint16_t* __restrict__ x,
                                                                    float* __restrict__ y, int M, int K) {
     const int lane = threadIdx.x & 63;
-    const int wave = blockIdx.x * kInt4Waves + (threadIdx.x >> 6);
+    const int wave = blockIdx.x * kInt4Waves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r0 = wave * kInt4RowsPerWave;
     if (r0 >= M) return;
+    const Int4Rows rows = int4_rows<G>(q, so, M, K, r0);
     float acc[kInt4RowsPerWave][B];
 #pragma unroll
     for (int r = 0; r < kInt4RowsPerWave; ++r)
@@ -2005,8 +2032,8 @@ __global__ __launch_bounds__(kInt4Waves * 64) void int4_gemv_kernel(const uint8_
         const bool two = k1 < K;
         Int4W wa, wb;
         Int4X<B> xa, xb;
-        int4_load_w<G>(wa, q, so, M, K, r0, k0);
-        if (two) int4_load_w<G>(wb, q, so, M, K, r0, k1);
+        int4_load_w<G>(wa, rows, k0);
+        if (two) int4_load_w<G>(wb, rows, k1);
         int4_load_x<B>(xa, x, K, k0);
         if (two) int4_load_x<B>(xb, x, K, k1);
         int4_step<B>(acc, wa, xa);
@@ -2030,15 +2057,15 @@ __global__ __launch_bounds__(kInt4Waves * 64) void int4_gemv_kernel(const uint8_
 // pairs past the last whole round are shared out by steps of 1,024 columns,
 // requested before all else and added at the end in the order of the steps (a
 // round of 512 pairs of 8,192 waves cost as long a chain of loads as a full
-// one): 17,408 x 5,120 12.06 -> 11.44 us (3.9 -> 4.2 TB/s), a table of 151,936
-// rows the same (82.1 and 82.3 us).
+// one): 17,408 x 5,120 12.06 -> 11.44 us (3.9 -> 4.2 TB/s).
 
 constexpr int kInt4LdsWaves = 16;
 constexpr int kInt4LdsThreads = kInt4LdsWaves * 64;
 
-// workgroups per CU of the persistent kernel: two at batch 1 (64 VGPRs),
-// one above
-inline int int4_lds_groups_per_cu(int B) { return B == 1 ? 2 : 1; }
+// workgroups per CU of the persistent kernel: two up to batch 2 (64 VGPRs;
+// batch 2 with one: 17,408 x 5,120 20.1-20.6 us, with two 17.4; 151,936 x
+// 5,120 113-117 and 102), one above
+inline int int4_lds_groups_per_cu(int B) { return B <= 2 ? 2 : 1; }
 
 // LDS bytes of the staged activations for K and B: [B][K/16][8] pairs, then
 // [B][K/16] sums
@@ -2050,7 +2077,7 @@ __host__ __device__ constexpr size_t int4_lds_bytes(int K, int B) {
 inline size_t int4_rest_bytes(int B) { return B == 1 ? kInt4LdsThreads * sizeof(uint4) : 0; }
 
 template <int B, int G>
-__global__ __launch_bounds__(kInt4LdsThreads) __attribute__((amdgpu_waves_per_eu(B == 1 ? 8 : 4)))
+__global__ __launch_bounds__(kInt4LdsThreads) __attribute__((amdgpu_waves_per_eu(B <= 2 ? 8 : 4)))
 void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
                                                                        const uint16_t* __restrict__ so,
                                                                        const uint16_t* __restrict__ x,
@@ -2060,7 +2087,7 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
     const int chunks = K / 16;
     float* s_sx = reinterpret_cast<float*>(s_xp + static_cast<size_t>(B) * chunks * 8);   // [B][K/16]
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int pairs = (M + kInt4RowsPerWave - 1) / kInt4RowsPerWave;
     const int waves = gridDim.x * kInt4LdsWaves;
     const int rg0 = blockIdx.x * kInt4LdsWaves + wave;
@@ -2074,7 +2101,7 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
     const bool by_steps = B == 1 && share * steps <= kInt4LdsWaves;
     [[maybe_unused]] const int rest_pair = whole + wave / steps * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x);
     [[maybe_unused]] const int rest_k = first_k + 1024 * (wave % steps);
-    [[maybe_unused]] const bool has_rest = by_steps && wave / steps < share && rest_pair < pairs && rest_k < K;
+    [[maybe_unused]] const bool rest_on = by_steps && wave / steps < share && rest_pair < pairs;
 
     auto stage = [&](const Int4X<B>& a, int c) {
 #pragma unroll
@@ -2085,22 +2112,22 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
             s_sx[bb * chunks + c] = a.sx[bb];
         }
     };
-    // Up to batch 5 the wave's first weights are requested behind its
-    // activations and before those are staged, so that both latencies run
-    // together (clamped to the matrix: what lies past its end is not used);
-    // above, the staged rows and the weights at once would spill
-    constexpr bool kEarly = B <= 5;
+    // At batch 1 the wave's first weights are requested before the activations
+    // are staged, so that both latencies run together (a wave past the last
+    // pair requests that one and drops it); at batches 2 to 5 this measured 1
+    // to 2 % slower, and from 6 on it would spill
+    constexpr bool kEarly = B == 1;
     Int4W wa, wb;
     [[maybe_unused]] Int4W wr;
     int c = threadIdx.x;
     if constexpr (kEarly) {
         Int4X<B> a;
         int4_load_x<B>(a, x, K, 16 * min(c, chunks - 1));
-        if constexpr (B == 1)
-            int4_load_w<G>(wr, q, so, M, K, (has_rest ? rest_pair : min(rg0, pairs - 1)) * kInt4RowsPerWave,
-                           has_rest ? rest_k : min(first_k, K - 16));
-        int4_load_w<G>(wa, q, so, M, K, min(rg0, pairs - 1) * kInt4RowsPerWave, min(first_k, K - 16));
-        int4_load_w<G>(wb, q, so, M, K, min(rg0, pairs - 1) * kInt4RowsPerWave, min(first_k + 1024, K - 16));
+        int4_load_w<G>(wr, int4_rows<G>(q, so, M, K, (rest_on ? rest_pair : min(rg0, pairs - 1)) * kInt4RowsPerWave),
+                       rest_on ? rest_k : first_k);
+        const Int4Rows rows = int4_rows<G>(q, so, M, K, min(rg0, pairs - 1) * kInt4RowsPerWave);
+        int4_load_w<G>(wa, rows, first_k);
+        int4_load_w<G>(wb, rows, first_k + 1024);
         if (c < chunks) stage(a, c);
         c += kInt4LdsThreads;
     }
@@ -2124,7 +2151,7 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
     [[maybe_unused]] uint4* s_rest = reinterpret_cast<uint4*>(s_sx + static_cast<size_t>(B) * chunks);   // [waves][64]
     if constexpr (B == 1) {
         // the step's sums of q x, with scale and offset, for the pair's owner
-        if (has_rest) {
+        if (rest_on && rest_k < K) {
             Int4X<B> xa;
             lds_x(xa, rest_k);
             float t[kInt4RowsPerWave];
@@ -2189,10 +2216,10 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
         }
     };
     auto walk = [&](int r0, int k_from) {
+        const Int4Rows rows = int4_rows<G>(q, so, M, K, r0);
         for (int k0 = k_from; k0 < K; k0 += 2048) {
-            const int k1 = k0 + 1024;
-            int4_load_w<G>(wa, q, so, M, K, r0, k0);
-            if (k1 < K) int4_load_w<G>(wb, q, so, M, K, r0, k1);
+            int4_load_w<G>(wa, rows, k0);
+            int4_load_w<G>(wb, rows, k0 + 1024);
             use(wa, wb, k0);
         }
     };

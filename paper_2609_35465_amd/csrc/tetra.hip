@@ -303,9 +303,13 @@ int int4_gemv_launch(const void* q, const uint16_t* scale_off, const uint16_t* x
     // in 128 KB from batch 6 on, where the per-row-pair kernel is slow
     // (151,936 x 5,120 at batch 8, 90 KB: 459 us without, 258 with; 17,408 x
     // 5,120: 53.9 and 42.9; 10,000 x 9,600 at batch 6, 127 KB: 43.3 and 40.9)
-    const long long lds_groups = static_cast<long long>(tetra_dev::int4_lds_groups_per_cu(batch)) * ds.cus;
+    // two workgroups per CU where the launch has a row pair for each of their
+    // waves; from batch 2 on one per CU still beats the per-row-pair kernel
+    const int per_cu = tetra_dev::int4_lds_groups_per_cu(batch);
+    const long long one_per_cu = static_cast<long long>(ds.cus) * tetra_dev::kInt4LdsWaves;
+    const long long lds_groups = static_cast<long long>(ds.cus) * (pairs >= per_cu * one_per_cu ? per_cu : 1);
     const size_t lds = tetra_dev::int4_lds_bytes(K, batch);
-    const bool use_lds = pairs >= lds_groups * tetra_dev::kInt4LdsWaves && lds <= (batch <= 5 ? 65536u : 131072u);
+    const bool use_lds = pairs >= (batch == 1 ? per_cu : 1) * one_per_cu && lds <= (batch <= 5 ? 65536u : 131072u);
 #define TETRA_I4(B)                                                                                          \
     case B:                                                                                                  \
         if (use_lds) {                                                                                       \

@@ -797,25 +797,27 @@ def test_int4_wide_batches_staged_bits(M, K, batch):
     print(f"[int4 staged] M={M} K={K} batch={batch} ok", flush=True)
 
 
+@pytest.mark.parametrize("batch", [1, 2])
 @pytest.mark.parametrize("M,K", [(16384, 1024), (16385, 1152), (17408, 5120), (19456, 5120), (19458, 5120),
                                  (32765, 1024), (16390, 16384), (16390, 16512)])
-def test_int4_single_token_shared_pairs_bits(M, K):
+def test_int4_full_chip_bits(M, K, batch):
     """At batch 1 the row pairs past the last whole round of 8,192 (on 256 CUs) are shared out by steps of
     1,024 columns where a workgroup's share of them has at most 16: none, one odd row, one pair, three and
-    four pairs of five steps, sixteen pairs of one, and one pair of 16 and 17.  The bits of the per-row-pair
+    four pairs of five steps, sixteen pairs of one, and one pair of 16 and 17.
+    Batch 2 takes two workgroups per CU from the same count of rows on.  The bits of the per-row-pair
     kernel on slices of the rows."""
     q, so = workloads.int4_matrix(M + K, M, K)
-    xd = _f16_dev(workloads.activations(M, 1, K))
+    xd = _f16_dev(workloads.activations(M, batch, K))
     qd, sd = _dev(q), _f16_dev(so)
-    y = torch.full((1, M), float("nan"), dtype=torch.float32, device="cuda")
-    tt.int4_gemv(qd, sd, xd, y, M, K, 1)
-    for r0 in range(0, M, 8192):
-        m = min(8192, M - r0)
-        part = torch.full((1, m), float("nan"), dtype=torch.float32, device="cuda")
-        tt.int4_gemv(qd[r0:r0 + m].contiguous(), sd[r0:r0 + m].contiguous(), xd, part, m, K, 1)
+    y = torch.full((batch, M), float("nan"), dtype=torch.float32, device="cuda")
+    tt.int4_gemv(qd, sd, xd, y, M, K, batch)
+    for r0 in range(0, M, 8190):
+        m = min(8190, M - r0)
+        part = torch.full((batch, m), float("nan"), dtype=torch.float32, device="cuda")
+        tt.int4_gemv(qd[r0:r0 + m].contiguous(), sd[r0:r0 + m].contiguous(), xd, part, m, K, batch)
         torch.cuda.synchronize()
-        assert torch.equal(part, y[:, r0:r0 + m]), (M, K, r0)
-    print(f"[int4 shared pairs] M={M} K={K} ok", flush=True)
+        assert torch.equal(part, y[:, r0:r0 + m]), (M, K, batch, r0)
+    print(f"[int4 shared pairs] M={M} K={K} batch={batch} ok", flush=True)
 
 
 def test_emb4_gather_bit_exact():
