@@ -60,6 +60,10 @@ constexpr int kEncWaves = 6;                        // section + 3 * trial
 constexpr int kEncThreads = 64 * kEncWaves;
 constexpr int kEncBatch = 24;                       // blocks whose norms and words are formed together
 constexpr int kEncGroupsPerCU = 4;                  // 4 x 40 KB of LDS, 6 waves per SIMD
+// Factor that marks a block whose squared norm is zero or not finite (it gets
+// the word 0): below every factor of another block, which may be 0 for one
+// radius and not for the other
+constexpr double kEncZeroBlock = -1.0;
 
 struct EncodeArgs {
     const float* w;                                 // [n][24], block order
@@ -409,7 +413,7 @@ __device__ __forceinline__ int enc_smallest_key(const int* W1, const int* W2, co
 __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(6, 6))) void encode_kernel(const EncodeArgs a) {
     __shared__ __attribute__((aligned(16))) int s_wave[kEncWaves][kEncWaveWords];
     __shared__ float s_w[kEncBatch * 24];
-    __shared__ double s_f[2][kEncBatch];            // radius 2^16 / ||w||; zero: the block gets the word 0
+    __shared__ double s_f[2][kEncBatch];            // radius 2^16 / ||w|| (0 where it underflows), or kEncZeroBlock for both
     __shared__ int s_score[kEncWaves], s_key[kEncWaves];   // a wave's best sum of the join and its key
     __shared__ int s_pick[kEncBatch][2][4];         // per trial: key, rows of the three sections
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
@@ -442,12 +446,12 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(6, 
             const bool zero = !(n2 > 0.0) || !(n2 <= 1.0e300);
             const double rn = zero ? 1.0 : sqrt(n2);
 #pragma unroll
-            for (int q = 0; q < 2; ++q) s_f[q][blk] = zero ? 0.0 : a.alpha[q] * static_cast<double>(kEncScale) / rn;
+            for (int q = 0; q < 2; ++q) s_f[q][blk] = zero ? kEncZeroBlock : a.alpha[q] * static_cast<double>(kEncScale) / rn;
         }
         __syncthreads();
         for (int blk = 0; blk < nb; ++blk) {
             const double f = s_f[trial][blk];
-            if (f == 0.0) continue;                 // of both radii
+            if (f == kEncZeroBlock) continue;       // of both radii: every wave leaves out the barriers below, or none
             // read afresh for each block: what derives from the lane alone would
             // otherwise be kept in registers across the blocks, and spilled
             const int lane = lane_now();
@@ -564,7 +568,7 @@ __global__ __launch_bounds__(kEncThreads) __attribute__((amdgpu_waves_per_eu(6, 
             const int blk = lane_now();
             const size_t gb = b0 + blk;
             uint64_t word = 0;
-            if (s_f[0][blk] != 0.0) {
+            if (s_f[0][blk] != kEncZeroBlock) {
                 double best_c = 0.0;
                 int best_t = 0;
 #pragma unroll 1

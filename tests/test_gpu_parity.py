@@ -1175,6 +1175,27 @@ def test_encode_list_ends_ties_and_batches(n, radii):
     assert np.array_equal(got, want[at])
 
 
+@pytest.mark.parametrize("radii", [(13.0, 1e-300), (1e-300, 13.0), (1e-300, 5e-324), (5e-324, 25.0)])
+def test_encode_factor_underflow(radii):
+    """Radii so small that radius * 2^16 / ||w|| underflows to zero, for one
+    trial or for both, on blocks of norm near 1e38 beside ordinary, tiny and
+    zero ones: such a block is searched with targets 0, only a zero block gets
+    the word 0 unsearched, and every word equals the oracle's."""
+    rng = np.random.default_rng(78)
+    base = rng.standard_normal((6, 24)).astype(np.float32)
+    base[0] *= np.float32(5e37)
+    base[2] = 0.0
+    base[3] *= np.float32(7e37)
+    base[4] *= np.float32(1e-30)
+    factors = [[r * 65536.0 / float(np.sqrt((b.astype(np.float64) ** 2).sum())) for r in radii] for b in base[[0, 1, 3]]]
+    assert factors[0][int(radii[1] < radii[0])] == 0.0
+    want = oencoder.encode_blocks(base, 1.25, radii)
+    at = np.arange(60) % len(base)
+    got = _encode_gpu(base[at], np.full(len(at), 1.25, np.float32), radii=radii)
+    print(f"[encode underflow] radii={radii} mismatches={(got != want[at]).sum()}", flush=True)
+    assert np.array_equal(got, want[at])
+
+
 # ------------------------------------------------------------- the boundary
 
 def _child(mode):
