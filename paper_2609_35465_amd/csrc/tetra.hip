@@ -564,13 +564,13 @@ int gemm_launch(const uint8_t* codes, const uint16_t* row_scales, const uint16_t
 }
 
 // a prompt of N tokens: the kernel addresses a launch's activations with
-// 32-bit byte offsets, so prompts longer than that run as several launches of
-// whole token tiles
+// 32-bit byte offsets, so prompts longer than 2 GiB run as several launches, of
+// whole token tiles where that many tokens fit
 int gemm_slices(const void* codes, const uint16_t* row_scales, const uint16_t* x, float* y, int M, int K, int N,
                 const Shape& s, int cus, int max_workers, uint8_t* workspace, hipStream_t stream) {
     const long long most = 0x7FFFFFFFll / (2ll * K);
-    const long long tile = most >= 32 * tetra_dev::kPfMaxTG ? 32 * tetra_dev::kPfMaxTG : 32;
-    const long long slice = std::max<long long>(tile, most / tile * tile);
+    const long long tile = most >= 32 * tetra_dev::kPfMaxTG ? 32 * tetra_dev::kPfMaxTG : most >= 32 ? 32 : 1;
+    const long long slice = std::max<long long>(1, most / tile * tile);
     for (long long n = 0; n < N; n += slice) {
         const int cnt = static_cast<int>(std::min<long long>(slice, N - n));
         if (int st = gemm_launch(static_cast<const uint8_t*>(codes), row_scales, x + n * K, y + n * M, M, K, cnt, s, cus,

@@ -1019,6 +1019,36 @@ def test_gemm_token_slices():
     assert worst <= TOL and worst <= TOL_GEMM
 
 
+def test_gemm_rows_past_a_token_tile():
+    """Rows so long that 32 tokens' activations pass 4 GiB (K = 2^26 + 16): a
+    launch takes as many tokens as stay under 2 GiB, 15 of them.  One row of
+    random words (every 48-bit device word is legal); the activations are zero
+    but for 100 block columns at either end and the tail, which the oracle
+    sums."""
+    M, K, N = 1, 2 ** 26 + 16, 32
+    nblk, T = K // 24, K % 24
+    assert 2 * K * N > 2 ** 32 and T in (0, 8, 16)
+    gen = torch.Generator(device="cuda").manual_seed(0x7E7A_0091)
+    blob = torch.empty(tt.codes_bytes(M, K), dtype=torch.uint8, device="cuda").random_(0, 256, generator=gen)
+    tail_h = (np.random.default_rng(91).standard_normal((M, T)) * 1e-2).astype(np.float16)
+    if T:
+        blob[tt.tail_offset(M, K):] = torch.from_numpy(tail_h.view(np.uint8).ravel()).cuda()
+    words, _ = tt.unpack_rows(blob.cpu().numpy(), M, K)
+    sigma = np.full(M, 1e-2, np.float16)
+    cols = np.r_[0:2400, 24 * (nblk - 100):K]
+    blks = np.r_[0:100, nblk - 100:nblk]
+    xs = workloads.activations(92, N, len(cols))
+    xd = torch.zeros((N, K), dtype=torch.float16, device="cuda")
+    xd[:, torch.as_tensor(cols, device="cuda")] = _f16_dev(xs)
+    y = torch.full((N, M), float("nan"), dtype=torch.float32, device="cuda")
+    tt.gemm(blob, _f16_dev(sigma), xd, y, M, K, N, _gemm_ws())
+    torch.cuda.synchronize()
+    yr, norm = ogemv.gemv_f64(words[:, blks], sigma, tail_h, xs)
+    worst = float((np.abs(y.cpu().numpy().astype(np.float64) - yr) / norm).max())
+    print(f"[gemm long rows] M={M} K={K} N={N} worst={worst:.3e}", flush=True)
+    assert worst <= TOL_GEMM
+
+
 @pytest.mark.parametrize("M,K,N", [(1024, 5120, 203), (200, 1536, 1), (4096, 2400, 129), (2100, 256, 77)])
 def test_gemm_split_items_repeat_bitwise(M, K, N):
     """Items cut across workgroups (16 pieces each for 1024 x 5120 at 203 tokens,
