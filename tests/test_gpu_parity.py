@@ -993,15 +993,16 @@ def test_gemm_long_prompt_sampled():
 
 def test_gemm_token_slices():
     """A prompt one token longer than a launch's slice (the largest multiple
-    of 128 tokens whose activations stay under 2 GiB: 61,568 tokens of
-    K = 17408) runs as two launches; tokens on both sides of the boundary,
-    the first and the last, against the oracle (activations drawn on the
-    device by a seeded generator, the sampled token rows copied back for the
-    oracle)."""
-    M, K = 64, 17408
-    slice_tokens = ((0x7FFFFFFF // (2 * K)) // 128) * 128
+    of 256 tokens whose activations stay under 2 GiB: 61,440 tokens of K =
+    17416, one trailing block column and a tail of 16) runs as two launches;
+    the first tokens, both sides of the cut (the first launch's largest byte
+    offsets) and the last, against the oracle (activations drawn on the device
+    by a seeded generator, the sampled token rows copied back for the oracle)."""
+    M, K = 64, 17416
+    slice_tokens = ((0x7FFFFFFF // (2 * K)) // 256) * 256
     N = slice_tokens + 1
-    assert slice_tokens * K * 2 < 2 ** 31 <= (slice_tokens + 128) * K * 2
+    assert slice_tokens == 61440 and K // 24 % 4 == 1 and K % 24 == 16
+    assert slice_tokens * K * 2 < 2 ** 31 <= (slice_tokens + 256) * K * 2
     words, sigma, tail = workloads.tetra_matrix(workloads.seed_for(3, 11), M, K)
     pk = Packed(words, sigma, tail, K)
     gen = torch.Generator(device="cuda").manual_seed(0x7E7A_0090)
@@ -1009,7 +1010,7 @@ def test_gemm_token_slices():
     y = torch.empty((N, M), dtype=torch.float32, device="cuda")
     tt.gemm(pk.blob, pk.sigma, xd, y, M, K, N, _gemm_ws())
     torch.cuda.synchronize()
-    toks = np.array([0, 1, slice_tokens - 2, slice_tokens - 1, slice_tokens])
+    toks = np.array([0, 1, slice_tokens - 257, slice_tokens - 256, slice_tokens - 2, slice_tokens - 1, slice_tokens])
     xs = xd[torch.as_tensor(toks, device="cuda")].cpu().numpy()
     del xd
     yr, norm = ogemv.gemv_f64(pk.words, pk.sigma_h, pk.tail, xs)
