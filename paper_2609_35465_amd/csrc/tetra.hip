@@ -517,12 +517,16 @@ int gemm_launch(const uint8_t* codes, const uint16_t* row_scales, const uint16_t
     const long long halves = static_cast<long long>((s.tiles + 1) / 2) * token_tiles;    // S = 2: of 128 rows
     if (halves >= (1ll << 31)) return TETRA_EINVAL;
     // S = 1 takes rounds of `cus` whole items; S = 2 spreads the chunks evenly
-    // but stages the activations twice as often and adds pieces.  Measured:
-    // rounds 3/4 full, 12288 x 4096 by 1024 tokens, 136 us against 146; 5/8
-    // full, 5120 x 5120 by 2048, 157 against 155; 3/8, 12288 x 4096 by 512,
-    // 120 against 88
+    // over the workgroups that have piece slots, but stages the activations
+    // twice as often and adds pieces.  Measured with a full workspace: rounds
+    // 3/4 full, 12288 x 4096 by 1024 tokens, 136 us against 146; 5/8 full, 5120
+    // x 5120 by 2048, 157 against 155; 3/8, 12288 x 4096 by 512, 120 against
+    // 88.  A smaller workspace splits only where its workgroups outdo the whole
+    // chip's rounds in the same proportion: 17408 x 5120 by 203 tokens (68
+    // items) 127 us whole, split over 1, 64, 112 and 160 workgroups 10,455, 182,
+    // 117 and 88
     const long long rounds = (whole + cus - 1) / cus;
-    const bool split = max_workers > 0 && 3 * whole < 2 * rounds * cus;
+    const bool split = 3 * whole < 2 * rounds * max_workers;
     tetra_dev::GemmArgs a;
     a.codes = codes;
     a.sigma = row_scales;
@@ -601,7 +605,7 @@ int tetra_gemm(const void* codes, const uint16_t* row_scales, const uint16_t* x,
     Shape s;
     if (!shape_of(M, K, &s)) return TETRA_EINVAL;
     // piece slots for as many workgroups as the device holds and the workspace
-    // has room for; a workspace too small for one runs whole items only
+    // has room for (possibly none: gemm_launch then takes whole items)
     if (workspace_bytes < kMinWorkspace) return TETRA_EINVAL;
     int workers = ds.gemm_workers;
     while (workers > 0 && tetra_dev::gemm_workspace_bytes(workers) > workspace_bytes) --workers;

@@ -1104,6 +1104,37 @@ def test_gemm_token_groups_rows_and_workspaces(M, K, N, ws_bytes):
     assert torch.isfinite(y).all() and worst <= TOL_GEMM
 
 
+@pytest.mark.parametrize("M,K,N", [(1100, 480, 100), (2000, 1536, 300)])
+def test_gemm_small_workspaces_take_whole_items(M, K, N):
+    """Items are split only over half as many workgroups again as there are
+    whole items: with pieces of fewer in the workspace the product runs whole
+    items on the whole chip, the same bits as with no pieces at all, and past
+    that count it is split."""
+    whole = -(-M // 256) * -(-N // 256)
+    words, sigma, tail = workloads.tetra_matrix(workloads.seed_for(0, 14) + M, M, K)
+    pk = Packed(words, sigma, tail, K)
+    x = workloads.activations(M + N, N, K)
+    xd = _f16_dev(x)
+
+    def product(slots):
+        ws = torch.empty(max(131328, 256 + slots * 262144), dtype=torch.uint8, device="cuda")
+        y = torch.full((N, M), float("nan"), dtype=torch.float32, device="cuda")
+        tt.gemm(pk.blob, pk.sigma, xd, y, M, K, N, ws)
+        torch.cuda.synchronize()
+        return y
+
+    first = product(0)
+    rows = _sample_rows(M, np.random.default_rng(N), n=64)
+    ref, norm = ogemv.gemv_f64(words[rows], sigma[rows], tail[rows], x)
+    for slots in (1, whole - 1, whole, 3 * whole // 2, 3 * whole // 2 + 1, 4 * whole):
+        y = product(slots)
+        worst = float((np.abs(y.cpu().numpy()[:, rows].astype(np.float64) - ref) / norm).max())
+        same = torch.equal(y, first)
+        print(f"[gemm small workspaces] M={M} K={K} N={N} slots={slots} whole={same} worst={worst:.3e}", flush=True)
+        assert worst <= TOL_GEMM
+        assert same or 2 * slots > 3 * whole
+
+
 # ----------------------------------------------------------------- encoder
 
 from oracle import codec as ocodec, encoder as oencoder, tables as otables  # noqa: E402
