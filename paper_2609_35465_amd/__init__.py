@@ -168,6 +168,15 @@ def _first_stream():
     return raw
 
 
+def _forget_getters():
+    global _device, _raw_stream
+    _device = _raw_stream = None
+
+
+# a forked child asks torch.cuda again, which refuses the parent's GPU context there
+os.register_at_fork(after_in_child=_forget_getters)
+
+
 def _ptr(t):
     return None if t is None else t.data_ptr()
 

@@ -275,3 +275,26 @@ def test_kernel_hash_ignores_comments_only():
     src = 'int a = 1; // one\n/* block\n comment */ int b = 2;\n  \nasm("s // t"); // x\n'
     assert bench._code_only(src) == 'int a = 1;\n int b = 2;\nasm("s // t");'
     assert bench._code_only(src) != bench._code_only(src.replace("2;", "3;"))
+
+
+def test_forked_child_asks_torch_for_its_stream():
+    """The current stream's getters are kept once torch.cuda is up; a forked
+    child does not use the parent's (the GPU context they belong to does not
+    survive the fork) but asks torch.cuda, which raises there."""
+    saved = tt._device, tt._raw_stream
+    tt._device, tt._raw_stream = lambda: 0, lambda device: 7
+    try:
+        assert tt._stream(None) == 7
+        pid = os.fork()
+        if pid == 0:
+            kept = True
+            try:
+                kept = tt._stream(None) == 7
+            except BaseException:
+                kept = False
+            finally:
+                os._exit(1 if kept else 0)
+        assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 0
+        assert tt._stream(None) == 7
+    finally:
+        tt._device, tt._raw_stream = saved
