@@ -1916,12 +1916,27 @@ struct Int4X {
     float sx[B];
 };
 
+// the 16 activations of each batch row as they lie in memory
 template <int B>
-__device__ __forceinline__ void int4_load_x(Int4X<B>& a, const uint16_t* __restrict__ x, int K, int k0) {
+struct Int4Raw {
+    uint4 v[B][2];
+};
+
+template <int B>
+__device__ __forceinline__ void int4_load_x(Int4Raw<B>& a, const uint16_t* __restrict__ x, int K, int k0) {
 #pragma unroll
     for (int bb = 0; bb < B; ++bb) {
         const uint4* xs = reinterpret_cast<const uint4*>(x + static_cast<size_t>(bb) * K + k0);
-        const uint4 u = xs[0], v = xs[1];
+        a.v[bb][0] = xs[0];
+        a.v[bb][1] = xs[1];
+    }
+}
+
+template <int B>
+__device__ __forceinline__ void int4_pair_x(Int4X<B>& a, const Int4Raw<B>& raw) {
+#pragma unroll
+    for (int bb = 0; bb < B; ++bb) {
+        const uint4 u = raw.v[bb][0], v = raw.v[bb][1];
         const uint32_t n[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};   // pairs (2i, 2i+1)
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -2026,18 +2041,31 @@ __global__ __launch_bounds__(kInt4Waves * 64) void int4_gemv_kernel(const uint8_
 #pragma unroll
         for (int bb = 0; bb < B; ++bb) acc[r][bb] = 0.f;
     for (int k0 = 16 * lane; k0 < K; k0 += 2048) {
-        // two steps' loads before either step's arithmetic (the second step
-        // exists for every lane or for none when K is a multiple of 1024)
+        // both steps' loads before any arithmetic, the activations first: held
+        // there by the barrier, the compiler needs 122 VGPRs at batch 5 (four
+        // waves per SIMD) and 141 and 160 at batch 6 and 7 (three); left to
+        // itself it spread the loads over the arithmetic to reach 127 at batch
+        // 5 and took 170 at batch 6 (two waves).  Against that, 9,728 x 9,728
+        // at batch 5 46.9 -> 35.1 us, 5,120 x 1,024 at batch 6 9.8 -> 7.2,
+        // 1,024 x 17,408 at batch 7 28.5 -> 23.5; 64-bit addresses took 37.3,
+        // 7.2 and 23.9.  (The second step exists for every lane or for none
+        // when K is a multiple of 1024.)
         const int k1 = k0 + 1024;
         const bool two = k1 < K;
         Int4W wa, wb;
-        Int4X<B> xa, xb;
+        Int4Raw<B> ra, rb;
+        int4_load_x<B>(ra, x, K, k0);
+        if (two) int4_load_x<B>(rb, x, K, k1);
         int4_load_w<G>(wa, rows, k0);
         if (two) int4_load_w<G>(wb, rows, k1);
-        int4_load_x<B>(xa, x, K, k0);
-        if (two) int4_load_x<B>(xb, x, K, k1);
+        __builtin_amdgcn_sched_barrier(0);
+        Int4X<B> xa;
+        int4_pair_x<B>(xa, ra);
         int4_step<B>(acc, wa, xa);
-        if (two) int4_step<B>(acc, wb, xb);
+        if (two) {
+            int4_pair_x<B>(xa, rb);
+            int4_step<B>(acc, wb, xa);
+        }
     }
 #pragma unroll
     for (int r = 0; r < kInt4RowsPerWave; ++r)
@@ -2057,7 +2085,12 @@ __global__ __launch_bounds__(kInt4Waves * 64) void int4_gemv_kernel(const uint8_
 // pairs past the last whole round are shared out by steps of 1,024 columns,
 // requested before all else and added at the end in the order of the steps (a
 // round of 512 pairs of 8,192 waves cost as long a chain of loads as a full
-// one): 17,408 x 5,120 12.06 -> 11.44 us (3.9 -> 4.2 TB/s).
+// one).  Graph replays over 400 MB of matrices, 17,408 x 5,120: 14.0 us with
+// neither that nor the descriptors, 12.6 with both (3.8 TB/s).  Requesting the
+// first weights before the activations are staged made launches of one or two
+// rounds slower (16,384 x 1,024 5.3 -> 6.7 us, 16,384 x 2,560 7.7 -> 8.9,
+// 17,408 x 5,120 12.6 -> 13.4): the requests that turn out not to be needed
+// cost more than the latency they hide.
 
 constexpr int kInt4LdsWaves = 16;
 constexpr int kInt4LdsThreads = kInt4LdsWaves * 64;
@@ -2073,35 +2106,56 @@ __host__ __device__ constexpr size_t int4_lds_bytes(int K, int B) {
     return static_cast<size_t>(B) * (K / 16) * (8 * 4 + 4);
 }
 
+// fewest steps of a row pair for sharing the last round (with fewer its chain of
+// loads is too short): 17,408 rows by 1,024 columns 5.7 us walked, 6.2 shared, by
+// 1,536 7.0 and 7.4, by 2,560 8.7 and 8.5; 16,800 by 2,560 8.6 and 8.0
+constexpr int kInt4ShareSteps = 3;
+
 // LDS bytes after them, at batch 1: each wave's step of a shared row pair
 inline size_t int4_rest_bytes(int B) { return B == 1 ? kInt4LdsThreads * sizeof(uint4) : 0; }
+
+// How a launch of `groups` persistent workgroups takes its row pairs: pairs
+// 0 .. whole-1 by waves in turn; each workgroup shares out by steps the `share`
+// (or fewer) pairs whole + i groups + its index of the rest.
+struct Int4Split {
+    int pairs, whole, share, steps;
+    uint32_t inv_steps;                    // ceil(65536 / steps)
+};
+
+inline Int4Split int4_split(int M, int K, int B, long long groups) {
+    const long long waves = groups * kInt4LdsWaves;
+    Int4Split s;
+    s.pairs = (M - 1) / kInt4RowsPerWave + 1;
+    s.steps = (K + 1023) / 1024;
+    s.inv_steps = (65536u + s.steps - 1) / s.steps;
+    s.whole = static_cast<int>(s.pairs / waves * waves);
+    s.share = static_cast<int>((s.pairs - s.whole + groups - 1) / groups);
+    if (B > 1 || s.steps < kInt4ShareSteps || static_cast<long long>(s.share) * s.steps > kInt4LdsWaves) {
+        s.whole = s.pairs;
+        s.share = 0;
+    }
+    return s;
+}
 
 template <int B, int G>
 __global__ __launch_bounds__(kInt4LdsThreads) __attribute__((amdgpu_waves_per_eu(B <= 2 ? 8 : 4)))
 void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
                                                                        const uint16_t* __restrict__ so,
                                                                        const uint16_t* __restrict__ x,
-                                                                       float* __restrict__ y, int M, int K) {
+                                                                       float* __restrict__ y, int M, int K, Int4Split split) {
     extern __shared__ uint4 s_x4[];
     uint32_t* s_xp = reinterpret_cast<uint32_t*>(s_x4);                 // [B][K/16][8]
     const int chunks = K / 16;
     float* s_sx = reinterpret_cast<float*>(s_xp + static_cast<size_t>(B) * chunks * 8);   // [B][K/16]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int pairs = (M + kInt4RowsPerWave - 1) / kInt4RowsPerWave;
     const int waves = gridDim.x * kInt4LdsWaves;
-    const int rg0 = blockIdx.x * kInt4LdsWaves + wave;
     const int first_k = 16 * lane;
-
-    // The row pairs past the last whole round, when a workgroup's share of
-    // them has at most as many steps as it has waves: shared out by steps
-    [[maybe_unused]] const int steps = (K + 1023) / 1024;
-    const int whole = pairs / waves * waves;
-    const int share = (pairs - whole + static_cast<int>(gridDim.x) - 1) / static_cast<int>(gridDim.x);
-    const bool by_steps = B == 1 && share * steps <= kInt4LdsWaves;
-    [[maybe_unused]] const int rest_pair = whole + wave / steps * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x);
-    [[maybe_unused]] const int rest_k = first_k + 1024 * (wave % steps);
-    [[maybe_unused]] const bool rest_on = by_steps && wave / steps < share && rest_pair < pairs;
+    // this wave's step of a shared row pair, if it has one
+    [[maybe_unused]] const int nth = static_cast<int>(static_cast<uint32_t>(wave) * split.inv_steps >> 16);   // wave / steps
+    [[maybe_unused]] const int rest_pair = split.whole + nth * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x);
+    [[maybe_unused]] const int rest_k = first_k + 1024 * (wave - nth * split.steps);
+    [[maybe_unused]] const bool rest_on = B == 1 && nth < split.share && rest_pair < split.pairs;
 
     auto stage = [&](const Int4X<B>& a, int c) {
 #pragma unroll
@@ -2112,28 +2166,15 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
             s_sx[bb * chunks + c] = a.sx[bb];
         }
     };
-    // At batch 1 the wave's first weights are requested before the activations
-    // are staged, so that both latencies run together (a wave past the last
-    // pair requests that one and drops it); at batches 2 to 5 this measured 1
-    // to 2 % slower, and from 6 on it would spill
-    constexpr bool kEarly = B == 1;
-    Int4W wa, wb;
+    // a shared pair's weights are requested before the activations are staged
     [[maybe_unused]] Int4W wr;
-    int c = threadIdx.x;
-    if constexpr (kEarly) {
+    if constexpr (B == 1)
+        if (rest_on) int4_load_w<G>(wr, int4_rows<G>(q, so, M, K, rest_pair * kInt4RowsPerWave), rest_k);
+    for (int c = threadIdx.x; c < chunks; c += kInt4LdsThreads) {
+        Int4Raw<B> raw;
         Int4X<B> a;
-        int4_load_x<B>(a, x, K, 16 * min(c, chunks - 1));
-        int4_load_w<G>(wr, int4_rows<G>(q, so, M, K, (rest_on ? rest_pair : min(rg0, pairs - 1)) * kInt4RowsPerWave),
-                       rest_on ? rest_k : first_k);
-        const Int4Rows rows = int4_rows<G>(q, so, M, K, min(rg0, pairs - 1) * kInt4RowsPerWave);
-        int4_load_w<G>(wa, rows, first_k);
-        int4_load_w<G>(wb, rows, first_k + 1024);
-        if (c < chunks) stage(a, c);
-        c += kInt4LdsThreads;
-    }
-    for (; c < chunks; c += kInt4LdsThreads) {
-        Int4X<B> a;
-        int4_load_x<B>(a, x, K, 16 * c);
+        int4_load_x<B>(raw, x, K, 16 * c);
+        int4_pair_x<B>(a, raw);
         stage(a, c);
     }
     __syncthreads();
@@ -2199,28 +2240,24 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
             if (bb & 1) __builtin_amdgcn_sched_barrier(0);
         }
     };
-    auto use = [&](const Int4W& a, const Int4W& b, int k0) {
-        const int k1 = k0 + 1024;
+    auto use = [&](const Int4W& w, int k) {
         if constexpr (B >= 6) {
-            step_by_two(a, k0);
-            if (k1 < K) step_by_two(b, k1);
+            step_by_two(w, k);
         } else {
-            // each step's activations just before the step (one register set)
+            // the step's activations just before it (one register set)
             Int4X<B> xa;
-            lds_x(xa, k0);
-            int4_step<B>(acc, a, xa);
-            if (k1 < K) {
-                lds_x(xa, k1);
-                int4_step<B>(acc, b, xa);
-            }
+            lds_x(xa, k);
+            int4_step<B>(acc, w, xa);
         }
     };
-    auto walk = [&](int r0, int k_from) {
+    auto walk = [&](int r0) {
         const Int4Rows rows = int4_rows<G>(q, so, M, K, r0);
-        for (int k0 = k_from; k0 < K; k0 += 2048) {
-            int4_load_w<G>(wa, rows, k0);
-            int4_load_w<G>(wb, rows, k0 + 1024);
-            use(wa, wb, k0);
+        Int4W wa, wb;
+        for (int k = first_k; k < K; k += 2048) {
+            int4_load_w<G>(wa, rows, k);
+            int4_load_w<G>(wb, rows, k + 1024);
+            use(wa, k);
+            if (k + 1024 < K) use(wb, k + 1024);
         }
     };
     auto finish = [&](int r0) {
@@ -2232,29 +2269,20 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
                 if (lane == 0 && r0 + r < M) y[static_cast<size_t>(bb) * M + r0 + r] = v;
             }
     };
-    const int end = by_steps ? whole : pairs;
-    int rg = rg0;
-    if (kEarly && rg < end) {
+    for (int rg = blockIdx.x * kInt4LdsWaves + wave; rg < split.whole; rg += waves) {
         clear();
-        if (first_k < K) use(wa, wb, first_k);
-        walk(rg * kInt4RowsPerWave, first_k + 2048);
-        finish(rg * kInt4RowsPerWave);
-        rg += waves;
-    }
-    for (; rg < end; rg += waves) {
-        clear();
-        walk(rg * kInt4RowsPerWave, first_k);
+        walk(rg * kInt4RowsPerWave);
         finish(rg * kInt4RowsPerWave);
     }
     if constexpr (B == 1) {
-        if (!by_steps || share == 0) return;
+        if (split.share == 0) return;
         __syncthreads();
-        const int pair = whole + wave * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x);
-        if (wave >= share || pair >= pairs) return;
+        const int pair = split.whole + wave * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x);
+        if (wave >= split.share || pair >= split.pairs) return;
         clear();
         // a lane's steps in the order one wave would have taken them
         for (int s = 0; first_k + 1024 * s < K; ++s) {
-            const uint4 t = s_rest[(wave * steps + s) * 64 + lane];
+            const uint4 t = s_rest[(wave * split.steps + s) * 64 + lane];
             const float sx = s_sx[(first_k + 1024 * s) / 16];
             acc[0][0] = fmaf(f16(static_cast<uint16_t>(t.y)), __builtin_bit_cast(float, t.x),
                              fmaf(f16(static_cast<uint16_t>(t.y >> 16)), sx, acc[0][0]));

@@ -297,24 +297,31 @@ int int4_gemv_launch(const void* q, const uint16_t* scale_off, const uint16_t* x
     const long long grid = (pairs + tetra_dev::kInt4Waves - 1) / tetra_dev::kInt4Waves;
     if (grid > 0x7FFFFFFFLL) return TETRA_EINVAL;
     const uint8_t* qb = static_cast<const uint8_t*>(q);
-    // a launch of at least one row pair per wave of a full chip of persistent
+    // A launch of at least one row pair per wave of a full chip of persistent
     // workgroups stages the activations in LDS, when they fit: in 64 KB up to
     // batch 5 (10,000 x 9,600 at batch 5, 105 KB: 33.4 us without, 35.9 with),
     // in 128 KB from batch 6 on, where the per-row-pair kernel is slow
     // (151,936 x 5,120 at batch 8, 90 KB: 459 us without, 258 with; 17,408 x
-    // 5,120: 53.9 and 42.9; 10,000 x 9,600 at batch 6, 127 KB: 43.3 and 40.9)
-    // two workgroups per CU where the launch has a row pair for each of their
-    // waves; from batch 2 on one per CU still beats the per-row-pair kernel
+    // 5,120: 53.9 and 42.9; 10,000 x 9,600 at batch 6, 127 KB: 43.3 and 40.9).
+    // At batch 6 and 7 its rounds have to be two thirds full: 9,728 x 5,120
+    // (4,864 pairs on 4,096 waves) takes 25.5 and 28.5 us staged and 22.8 and
+    // 25.4 without, 11,000 x 5,120 (67 % full) 25.6 and 28.7 staged, 25.9 and
+    // 29.0 without; at batch 8 9,728 x 5,120 takes 31.5 staged and 32.2 without.
+    // Two workgroups per CU where the launch has a row pair for each of their
+    // waves; from batch 2 on one per CU still beats the per-row-pair kernel.
     const int per_cu = tetra_dev::int4_lds_groups_per_cu(batch);
     const long long one_per_cu = static_cast<long long>(ds.cus) * tetra_dev::kInt4LdsWaves;
     const long long lds_groups = static_cast<long long>(ds.cus) * (pairs >= per_cu * one_per_cu ? per_cu : 1);
     const size_t lds = tetra_dev::int4_lds_bytes(K, batch);
-    const bool use_lds = pairs >= (batch == 1 ? per_cu : 1) * one_per_cu && lds <= (batch <= 5 ? 65536u : 131072u);
+    const long long rounds = (pairs + one_per_cu - 1) / one_per_cu;
+    const bool use_lds = pairs >= (batch == 1 ? per_cu : 1) * one_per_cu && lds <= (batch <= 5 ? 65536u : 131072u) &&
+                         !((batch == 6 || batch == 7) && 3 * pairs < 2 * rounds * one_per_cu);
 #define TETRA_I4(B)                                                                                          \
     case B:                                                                                                  \
         if (use_lds) {                                                                                       \
             hipLaunchKernelGGL((tetra_dev::int4_gemv_lds_kernel<B, G>), dim3(static_cast<unsigned>(lds_groups)), \
-                               dim3(tetra_dev::kInt4LdsThreads), lds + tetra_dev::int4_rest_bytes(B), stream, qb, scale_off, x, y, M, K);    \
+                               dim3(tetra_dev::kInt4LdsThreads), lds + tetra_dev::int4_rest_bytes(B), stream, qb,        \
+                               scale_off, x, y, M, K, tetra_dev::int4_split(M, K, B, lds_groups));               \
             break;                                                                                           \
         }                                                                                                    \
         hipLaunchKernelGGL((tetra_dev::int4_gemv_kernel<B, G>), dim3(static_cast<unsigned>(grid)),           \

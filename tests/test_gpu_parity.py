@@ -777,11 +777,12 @@ def test_head4_gemv_full_size_sampled():
 # ------------------------------------------------------------------- emb4
 
 @pytest.mark.parametrize("batch", [2, 5, 6, 7, 8])
-@pytest.mark.parametrize("M,K", [(8191, 1152), (8192, 1024), (8194, 7296)])
+@pytest.mark.parametrize("M,K", [(8191, 1152), (8192, 1024), (8194, 7296), (10922, 1024), (10924, 1152)])
 def test_int4_wide_batches_staged_bits(M, K, batch):
     """Launches on either side of the row count from which the activations are
     staged in LDS (8,192 rows on 256 CUs; up to 128 KB of them, which K = 7,296
-    at batch 8 passes): the bits of the per-row-pair kernel on slices of the
+    at batch 8 passes), and at batch 6 and 7 of two thirds of a second round
+    (10,923): the bits of the per-row-pair kernel on slices of the
     rows, for every batch row."""
     q, so = workloads.int4_matrix(M + K, M, K)
     x = workloads.activations(M + batch, batch, K)
@@ -799,11 +800,13 @@ def test_int4_wide_batches_staged_bits(M, K, batch):
 
 @pytest.mark.parametrize("batch", [1, 2])
 @pytest.mark.parametrize("M,K", [(16384, 1024), (16385, 1152), (17408, 5120), (19456, 5120), (19458, 5120),
-                                 (32765, 1024), (16390, 16384), (16390, 16512)])
+                                 (32765, 1024), (16390, 16384), (16390, 16512), (16390, 2048), (16385, 2176),
+                                 (21504, 2176), (21506, 2176)])
 def test_int4_full_chip_bits(M, K, batch):
     """At batch 1 the row pairs past the last whole round of 8,192 (on 256 CUs) are shared out by steps of
-    1,024 columns where a workgroup's share of them has at most 16: none, one odd row, one pair, three and
-    four pairs of five steps, sixteen pairs of one, and one pair of 16 and 17.
+    1,024 columns where a pair has three or more and a workgroup's share of them has at most 16: none, one
+    odd row of two steps, one pair, three and four pairs of five steps, sixteen pairs of one, one pair of 16,
+    17 and two, one odd row of three, and five and six pairs of three.
     Batch 2 takes two workgroups per CU from the same count of rows on.  The bits of the per-row-pair
     kernel on slices of the rows."""
     q, so = workloads.int4_matrix(M + K, M, K)
