@@ -193,8 +193,9 @@ def gemm_workspace_bytes() -> int:
 
 
 def gemm_workspace():
-    """A zero-filled workspace for tetra_gemm on the current device (a torch
-    uint8 tensor; torch allocates it, 256-byte aligned)."""
+    """A workspace for tetra_gemm on the current device (a torch uint8 tensor,
+    which torch aligns to 256 bytes; it comes zero-filled, but what it holds
+    before a call does not matter to the product)."""
     import torch
     n = gemm_workspace_bytes()
     if n == 0:

@@ -449,7 +449,12 @@ inline int gemv_waves(uint32_t total, int cus, int groups) {
 // one: 1536 x 1536 (64 columns) 8.4 -> 7.0 us at batch 1, 9.6 -> 7.7 at 2,
 // 11.4 -> 9.6 at 8; 4096 x 2560 (106) 9.9 -> 8.9, 11.3 -> 10.1, 14.7 -> 14.1;
 // 16384 x 2560 (256 tiles) 14.0 -> 9.5 at batch 1; 1024 x 5120 (213 columns)
-// 9.6 -> 11.7; 17408 x 1024 (272 tiles, 42 columns) 9.6 -> 10.1.
+// 9.6 -> 11.7; 17408 x 1024 (272 tiles, 42 columns) 9.6 -> 10.1.  With 1 to 256
+// tiles of 12 to 85 columns it takes 0.71-0.87 of the even split's time at batch
+// 1, 2, 3, 4 and 8, of 106 and 110 0.89-0.93 (256 tiles 0.63-0.70 up to batch 2,
+// 0.99 above), of 112 0.93-0.96 at batch 1 and 0.97-1.00 at batch 8.  A tile by
+// itself gains less, 0.85-0.98, or loses up to 9 % (0.6 us, at 32 and 33
+// columns), since the even split leaves it to one workgroup too.
 constexpr int kGemvTileColumns = 112;
 inline bool gemv_tile_per_group(int nblk, uint32_t tiles, int cus) {
     return nblk >= kGemvWaves && nblk <= kGemvTileColumns && tiles <= static_cast<uint32_t>(cus);
@@ -2139,21 +2144,19 @@ inline Int4Split int4_split(int M, int K, int B, long long groups) {
 
 template <int B, int G>
 __global__ __launch_bounds__(kInt4LdsThreads) __attribute__((amdgpu_waves_per_eu(B <= 2 ? 8 : 4)))
-void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
-                                                                       const uint16_t* __restrict__ so,
-                                                                       const uint16_t* __restrict__ x,
-                                                                       float* __restrict__ y, int M, int K, Int4Split split) {
+void int4_gemv_lds_kernel(const uint8_t* __restrict__ q, const uint16_t* __restrict__ so, const uint16_t* __restrict__ x,
+                          float* __restrict__ y, int M, int K, Int4Split split) {
     extern __shared__ uint4 s_x4[];
     uint32_t* s_xp = reinterpret_cast<uint32_t*>(s_x4);                 // [B][K/16][8]
     const int chunks = K / 16;
     float* s_sx = reinterpret_cast<float*>(s_xp + static_cast<size_t>(B) * chunks * 8);   // [B][K/16]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int waves = gridDim.x * kInt4LdsWaves;
     const int first_k = 16 * lane;
     // this wave's step of a shared row pair, if it has one
+    const int groups = static_cast<int>(gridDim.x), group = static_cast<int>(blockIdx.x);
     [[maybe_unused]] const int nth = static_cast<int>(static_cast<uint32_t>(wave) * split.inv_steps >> 16);   // wave / steps
-    [[maybe_unused]] const int rest_pair = split.whole + nth * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x);
+    [[maybe_unused]] const int rest_pair = split.whole + nth * groups + group;
     [[maybe_unused]] const int rest_k = first_k + 1024 * (wave - nth * split.steps);
     [[maybe_unused]] const bool rest_on = B == 1 && nth < split.share && rest_pair < split.pairs;
 
@@ -2269,7 +2272,7 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
                 if (lane == 0 && r0 + r < M) y[static_cast<size_t>(bb) * M + r0 + r] = v;
             }
     };
-    for (int rg = blockIdx.x * kInt4LdsWaves + wave; rg < split.whole; rg += waves) {
+    for (int rg = group * kInt4LdsWaves + wave; rg < split.whole; rg += groups * kInt4LdsWaves) {
         clear();
         walk(rg * kInt4RowsPerWave);
         finish(rg * kInt4RowsPerWave);
@@ -2277,7 +2280,7 @@ void int4_gemv_lds_kernel(const uint8_t* __restrict__ q,
     if constexpr (B == 1) {
         if (split.share == 0) return;
         __syncthreads();
-        const int pair = split.whole + wave * static_cast<int>(gridDim.x) + static_cast<int>(blockIdx.x);
+        const int pair = split.whole + wave * groups + group;
         if (wave >= split.share || pair >= split.pairs) return;
         clear();
         // a lane's steps in the order one wave would have taken them

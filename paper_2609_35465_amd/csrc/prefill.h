@@ -28,11 +28,11 @@
 // products.  Two waves share a SIMD (128 accumulators each): one wave alone
 // (64 rows, 512 registers) issues an instruction every five cycles at most
 // and was bound by that, 0.445 ms where this form takes 0.435 (12288 x 4096 by
-// 4096 tokens) and 2.7 us a chunk where it takes 2.3 (20 workgroups).  With S = 1 the waves hold 8 x 32 rows; with S = 2 they hold
-// 4 x 32 rows, and two waves share a row set, one for each window of a chunk,
-// their sums meeting in LDS at the end: half the rows per workgroup, for
-// launches that must be cut into pieces to fill the chip (a piece then is
-// half as large).
+// 4096 tokens) and 2.7 us a chunk where it takes 2.3 (20 workgroups).  With S =
+// 1 the waves hold 8 x 32 rows; with S = 2 they hold 4 x 32 rows, and two waves
+// share a row set, one for each window of a chunk, their sums meeting in LDS at
+// the end: half the rows per workgroup, for launches that must be cut into
+// pieces to fill the chip (a piece then is half as large).
 //
 // The activations go through LDS in chunks of 96 k (one group of four block
 // columns), double-buffered, one barrier per chunk: the next chunk's are
@@ -110,9 +110,9 @@ __device__ __forceinline__ uint32_t pf_part(const pf_u32x4& v, int i) {
     return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
 }
 
-// workspace of a launch with at most `workers` workgroups: a header that
-// nothing uses (eight bytes each, rounded up to 256; the size callers
-// allocate includes it), then two piece slots per workgroup
+// workspace of a launch with at most `workers` workgroups: eight bytes each,
+// rounded up to 256, that hold nothing (kept so that the sizes callers have
+// allocated go on holding the same pieces), then two piece slots per workgroup
 inline size_t gemm_header_bytes(int workers) {
     return (8 * static_cast<size_t>(workers) + 255) & ~static_cast<size_t>(255);
 }
@@ -316,12 +316,13 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2, 2
     const unsigned long long u1 = S == 1 ? 0 : pf_range_begin(blockIdx.x + 1, a);
     unsigned long long base = S == 1 ? 0 : pf_uniform(u0 - u0 % a.upi);
     ts.store(s_tab);
-    for (int item = S == 1 ? static_cast<int>(blockIdx.x) : __builtin_amdgcn_readfirstlane(static_cast<int>(base / a.upi));
+    for (int item = S == 1 ? static_cast<int>(blockIdx.x)
+                           : __builtin_amdgcn_readfirstlane(static_cast<int>(base / a.upi));
          S == 1 ? item < a.items : base < u1; item += S == 1 ? a.workers : 1, base += a.upi) {
         // this workgroup's units c0 .. c1-1 of the item
         const int c0 = S == 1 ? 0 : __builtin_amdgcn_readfirstlane(static_cast<int>((u0 > base ? u0 : base) - base));
-        const int c1 = S == 1 ? a.upi
-                              : __builtin_amdgcn_readfirstlane(static_cast<int>((u1 < base + a.upi ? u1 : base + a.upi) - base));
+        const unsigned long long last = u1 < base + a.upi ? u1 : base + a.upi;
+        const int c1 = S == 1 ? a.upi : __builtin_amdgcn_readfirstlane(static_cast<int>(last - base));
         const int irow = item / a.tgroups;
         const int n0 = (item - irow * a.tgroups) * (32 * TG);
         // the wave's row set; past the last tile it repeats that and stores nothing
@@ -372,7 +373,8 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2, 2
                 for (int j = 0; j < 2; ++j) {
                     if (S == 2 && j == 1) continue;
                     const int q = 2 * (S == 2 ? ksplit : j) + (ln >> 5);
-                    const tetra::WordLoc at = tetra::word_loc(a.nblk, 32 * (rset & 1) + (ln & 31), 4 * a.ng + min(q, a.rem - 1));
+                    const int col = 4 * a.ng + min(q, a.rem - 1);
+                    const tetra::WordLoc at = tetra::word_loc(a.nblk, 32 * (rset & 1) + (ln & 31), col);
                     w.lo[j] = *reinterpret_cast<const uint32_t*>(tb + at.lo_off);
                     w.hi[j] = *reinterpret_cast<const uint16_t*>(tb + at.hi_off);
                     if (q >= a.rem) {
@@ -390,8 +392,8 @@ __global__ __launch_bounds__(kPfThreads) __attribute__((amdgpu_waves_per_eu(2, 2
         };
         // the products of the window at `at` of the chunk xs with `cur`, and
         // between them the decode of the words lo, hi into `nxt`
-        auto window = [&](const uint8_t* xs, const uint32_t (&at)[3], const PfBlock& cur, PfBlock& nxt, uint32_t lo, uint32_t hi,
-                          auto&& also) {
+        auto window = [&](const uint8_t* xs, const uint32_t (&at)[3], const PfBlock& cur, PfBlock& nxt, uint32_t lo,
+                          uint32_t hi, auto&& also) {
             pf_for<kAhead>([&](auto s) {
                 if constexpr (s < kSlots) av[s] = frag(xs, at, s);
             });

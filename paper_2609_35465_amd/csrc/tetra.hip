@@ -215,7 +215,8 @@ int launch_gemv(const tetra_gemv_problem* probs, int n, const int* counts, int n
     int grid;
     if (n_phases == 1) {
         const int nblk = ch.prob[0].nblk;
-        const bool one_width = std::all_of(ch.prob, ch.prob + n, [&](const tetra_dev::GemvProblem& P) { return P.nblk == nblk; });
+        const bool one_width =
+            std::all_of(ch.prob, ch.prob + n, [&](const tetra_dev::GemvProblem& P) { return P.nblk == nblk; });
         ch.ph[0].waves = std::min(one_width && tetra_dev::gemv_tile_per_group(nblk, ch.ph[0].total / nblk, cus)
                                       ? static_cast<int>(ch.ph[0].total / nblk) * tetra_dev::kGemvWaves
                                       : tetra_dev::gemv_waves(ch.ph[0].total, cus, ds.gemv_groups[batch]),
@@ -320,8 +321,8 @@ int int4_gemv_launch(const void* q, const uint16_t* scale_off, const uint16_t* x
     case B:                                                                                                  \
         if (use_lds) {                                                                                       \
             hipLaunchKernelGGL((tetra_dev::int4_gemv_lds_kernel<B, G>), dim3(static_cast<unsigned>(lds_groups)), \
-                               dim3(tetra_dev::kInt4LdsThreads), lds + tetra_dev::int4_rest_bytes(B), stream, qb,        \
-                               scale_off, x, y, M, K, tetra_dev::int4_split(M, K, B, lds_groups));               \
+                               dim3(tetra_dev::kInt4LdsThreads), lds + tetra_dev::int4_rest_bytes(B), stream, qb, \
+                               scale_off, x, y, M, K, tetra_dev::int4_split(M, K, B, lds_groups));           \
             break;                                                                                           \
         }                                                                                                    \
         hipLaunchKernelGGL((tetra_dev::int4_gemv_kernel<B, G>), dim3(static_cast<unsigned>(grid)),           \
@@ -628,7 +629,7 @@ int tetra_gemm_noalloc(const void* codes, const uint16_t* row_scales, const uint
     static_assert(sizeof(tetra_dev::GemvChain) <= 4096, "kernel arguments");
     static_assert(kScratchBytes >= (8 * kScratchWorkers + 255) / 256 * 256 +
                                        sizeof(float) * static_cast<size_t>(kScratchWorkers) * 2 * tetra_dev::kPfSlot,
-                  "scratch holds the counters and pieces of kScratchWorkers workgroups");
+                  "scratch holds the pieces of kScratchWorkers workgroups");
     if (!codes || !row_scales || !x || !y || M < 1 || K < 24 || N < 1 || K % 8) return TETRA_EINVAL;
     if (!aligned(codes, 16) || !aligned(x, 16) || !aligned(row_scales, 2) || !aligned(y, 4)) return TETRA_EALIGN;
     int dev;

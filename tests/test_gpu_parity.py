@@ -42,7 +42,7 @@ _GEMM_WS = []
 
 
 def _gemm_ws():
-    """one zero-filled tetra_gemm workspace for the module (calls run on one stream)"""
+    """one tetra_gemm workspace for the module (calls run on one stream)"""
     if not _GEMM_WS:
         _GEMM_WS.append(tt.gemm_workspace())
     return _GEMM_WS[0]
@@ -1055,13 +1055,12 @@ def test_gemm_rows_past_a_token_tile():
 
 @pytest.mark.parametrize("M,K,N", [(1024, 5120, 203), (200, 1536, 1), (4096, 2400, 129), (2100, 256, 77)])
 def test_gemm_split_items_repeat_bitwise(M, K, N):
-    """Items cut across workgroups (16 pieces each for 1024 x 5120 at 203 tokens,
-    one unit per workgroup for 200 x 1536 at one token, two-tile items with an
-    odd tile count for 2100 x 256, whose last item has no second tile): two
-    calls in a row,
-    with a GEMV on the same device between them, give the same bits, so the
-    piece counters are back at zero after each launch and the pieces are
-    added in a fixed order."""
+    """Items of 128 rows cut across workgroups (eight pieces each for 1024 x 5120
+    at 203 tokens, 200 x 1536 at one and 4096 x 2400 at 129; one chunk per
+    workgroup for 2100 x 256, whose last item has one tile and whose items end
+    in two trailing block columns): two calls in a row, with a GEMV on the same
+    device between them, give the same bits, so the pieces are added in a fixed
+    order, and no piece of another call is read."""
     words, sigma, tail = workloads.tetra_matrix(workloads.seed_for(0, 7) + M + N, M, K)
     pk = Packed(words, sigma, tail, K)
     x = workloads.activations(M + N, N, K)
