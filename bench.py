@@ -387,8 +387,12 @@ def cpu_baseline(torch, tt, plan, seconds):
 
 KERNEL_SOURCES = ("paper_2609_35465_amd/csrc/kernels.h", "paper_2609_35465_amd/csrc/device_tables.h",
                   "paper_2609_35465_amd/csrc/word_format.h")
+AFTER_GEMV = "// ----------------------------------------------------- int4 projections"   # in kernels.h
 LAUNCH_SOURCE = "paper_2609_35465_amd/csrc/tetra.hip"
 TRAFFIC_PROFILE = "profiles/gemv_kernel_qwen3-14b-40-layers_traffic.md"
+ENCODER_SOURCES = ("paper_2609_35465_amd/csrc/encoder.h", "paper_2609_35465_amd/csrc/gen_tables.cpp",
+                   "paper_2609_35465_amd/csrc/table_layout.h", "paper_2609_35465_amd/csrc/word_format.h")
+ENCODER_PROFILE = "profiles/encode_kernel_gaussian-20000-blocks_kernel-trace.md"
 
 
 def _code_only(text):
@@ -410,13 +414,17 @@ def _code_only(text):
 
 def kernel_source_hash():
     """sha256 over what decides the measured kernel: the device sources of the
-    GEMV, its launch planning (the `launch_gemv` function of the library) and
-    the compiler flags, comments left out."""
+    GEMV (kernels.h up to the kernels that follow it), its launch planning (the
+    `launch_gemv` function of the library) and the compiler flags, comments
+    left out."""
     import hashlib
     from paper_2609_35465_amd import build as _build
     h = hashlib.sha256()
     for f in KERNEL_SOURCES:
-        h.update(_code_only(open(os.path.join(ROOT, f), encoding="utf-8").read()).encode())
+        text = open(os.path.join(ROOT, f), encoding="utf-8").read()
+        if f.endswith("kernels.h"):
+            text = text[:text.index(AFTER_GEMV)]
+        h.update(_code_only(text).encode())
     lines = open(os.path.join(ROOT, LAUNCH_SOURCE), encoding="utf-8").read().split("\n")
     start = next(i for i, l in enumerate(lines) if l.startswith("int launch_gemv("))
     end = next(i for i in range(start, len(lines)) if lines[i] == "}")
@@ -425,11 +433,23 @@ def kernel_source_hash():
     return h.hexdigest()
 
 
-def recorded_traffic(args, layers):
-    """HBM bytes per gemv launch from the committed counter profile, or None
-    when the profile is absent, was taken on another workload, or the kernel
-    sources have changed since it was taken."""
-    path = os.path.join(ROOT, TRAFFIC_PROFILE)
+def encoder_source_hash():
+    """sha256 over the encoder's device sources, its tables and the compiler
+    flags, comments left out."""
+    import hashlib
+    from paper_2609_35465_amd import build as _build
+    h = hashlib.sha256()
+    for f in ENCODER_SOURCES:
+        h.update(_code_only(open(os.path.join(ROOT, f), encoding="utf-8").read()).encode())
+    h.update(" ".join(_build.HIP_FLAGS).encode())
+    return h.hexdigest()
+
+
+def profile_record(profile, want, key):
+    """The integer `key` of a committed counter profile, or None when the
+    profile is absent or any entry of `want` (workload, source hash) differs
+    from what it records."""
+    path = os.path.join(ROOT, profile)
     if not os.path.exists(path):
         return None
     rec = {}
@@ -437,15 +457,21 @@ def recorded_traffic(args, layers):
         if line.startswith("- ") and ": " in line:
             k, v = line[2:].strip().split(": ", 1)
             rec[k] = v.strip().strip("`")
-    want = {"source_sha256": kernel_source_hash(), "mode": args.mode,
-            "batch": str(args.batch), "model": args.model, "layers": str(layers),
-            "workload": args.workload}
     if any(rec.get(k) != v for k, v in want.items()):
         return None
     try:
-        return int(rec["traffic_bytes_per_launch"])
+        return int(rec[key])
     except (KeyError, ValueError):
         return None
+
+
+def recorded_traffic(args, layers):
+    """HBM bytes per gemv launch from the committed counter profile, or None
+    when it was taken on another workload or another kernel."""
+    return profile_record(TRAFFIC_PROFILE,
+                          {"source_sha256": kernel_source_hash(), "mode": args.mode, "batch": str(args.batch),
+                           "model": args.model, "layers": str(layers), "workload": args.workload},
+                          "traffic_bytes_per_launch")
 
 
 HEAD_ROWS, HEAD_DIM = 151936, 5120
@@ -763,14 +789,17 @@ def main_encode(args, torch, tt):
     e1.record(stream)
     torch.cuda.synchronize()
     ms_step = e0.elapsed_time(e1) / steps
-    # the kernel's work: 6,780 VALU wave instructions per block (SQ_INSTS_VALU
-    # over this workload), a lane operation each; beside it the definition's:
-    # every (p, pattern byte) pair scores every row of each section's lists
-    # (4096 + 2048 + 4096 rows) with 8 additions, per trial radius, which the
-    # kernel does not carry out (it takes maxima over the cost levels)
+    # the issued work: VALU wave instructions per launch from the committed
+    # counter profile (SQ_INSTS_VALU over this workload), 64 lanes each; beside it
+    # the definition's: every (p, pattern byte) pair scores every row of each
+    # section's lists (4096 + 2048 + 4096 rows) with 8 additions, per trial
+    # radius, which the kernel does not carry out (it takes maxima over the cost
+    # levels)
+    insts = profile_record(ENCODER_PROFILE, {"source_sha256": encoder_source_hash(), "blocks": str(n)},
+                           "valu_wave_instructions_per_launch")
     adds = 2.0 * 256 * (4096 + 2048 + 4096) * 8 * n
-    executed = 6780.0 * 64 * n
-    tops = executed / (ms_step * 1e-3) / 1e12
+    issued = None if insts is None else 64.0 * insts
+    tops = None if insts is None else issued / (ms_step * 1e-3) / 1e12
     tops_def = adds / (ms_step * 1e-3) / 1e12
     out_j = {
         "metric": "Tetra encoder throughput, 24-weight blocks per second", "value": round(n / (ms_step * 1e-3), 1),
@@ -781,13 +810,15 @@ def main_encode(args, torch, tt):
                                f"{tt.ENCODE_RADII[1]:g}", "blocks": n},
         "retention": round(oencoder.retention(mse), 5), "mse_per_weight": round(mse, 6),
         "parity_sampled_mismatches": mism,
-        "roofline": {"bound": "alu", "achieved": round(tops, 3), "peak": round(VALU32_PEAK_TOPS, 1),
-                     "unit": "Tops/s", "frac": round(tops / VALU32_PEAK_TOPS, 4), "traffic": None,
+        "roofline": {"bound": "alu", "achieved": None if tops is None else round(tops, 3),
+                     "peak": round(VALU32_PEAK_TOPS, 1), "unit": "Tops/s",
+                     "frac": None if tops is None else round(tops / VALU32_PEAK_TOPS, 4), "traffic": None,
                      "kernel": "encode_kernel", "avg_launch_us": round(ms_step * 1e3, 1),
-                     "ops": "executed VALU lane operations (6,780 wave instructions per block)",
-                     "ops_per_launch": executed,
-                     "effective": {"achieved": round(tops_def, 3), "frac": round(tops_def / VALU32_PEAK_TOPS, 4),
-                                   "ops": "the definition's 8 additions per (p, byte) pair and list row",
+                     "ops": "VALU lane operations issued (SQ_INSTS_VALU x 64; null when the kernel has changed since)",
+                     "ops_per_launch": issued,
+                     "effective": {"achieved": round(tops_def, 3),
+                                   "ops": "the definition's 8 additions per (p, byte) pair and list row "
+                                          "(not carried out one by one, so no fraction of the peak)",
                                    "ops_per_launch": adds}},
     }
     if not args.no_cpu_baseline:
