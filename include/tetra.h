@@ -257,8 +257,8 @@ int tetra_decode(const void* words, size_t n, int8_t* y_out, float* blk_scale_ou
  *   y: device fp32 [N][M], fully overwritten
  * N >= 1; a prompt whose activations pass 2 GiB runs as several launches.
  * Meant for N well above TETRA_MAX_BATCH.  The rounded weights make an error of
- * at most 2^-11 of the row's sum |w x| (4.9e-4; up to 2e-5 is seen on products
- * of 1,536 columns and more, where the roundings average out), tetra_gemv's is
+ * at most 2^-11 of the row's sum |w x| (4.9e-4; 2e-4 is seen at one block column
+ * and 2e-5 at 5,120 columns, as the roundings average out), tetra_gemv's is
  * below 1e-5.  The split of the work over workgroups follows M, K, N, the CU
  * count and the workspace, so a token's result can change in the last bits with
  * them (it never changes from run to run).

@@ -54,8 +54,8 @@
 //
 // Measured against a kernel of four waves with 32x32x8 products, each lane
 // decoding half a block, at two workgroups per CU: 12288 x 4096 by 4096
-// tokens 0.86 -> 0.43 ms (950 TFLOP/s, the clock then near 1.6 GHz: the chip
-// is at its power limit), 17408 x 5120 by 203 tokens 125 -> 74 us.
+// tokens 0.86 -> 0.42 ms (992 TFLOP/s, the clock then at 1.8 to 1.9 GHz: the
+// chip is at its power limit), 17408 x 5120 by 203 tokens 125 -> 71 us.
 #pragma once
 
 #include <type_traits>
